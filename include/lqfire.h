@@ -348,8 +348,10 @@ int32_t lq_batch_size(const lq_batch* b);
 int lq_batch_step(lq_batch* b, int64_t n_steps, lq_fire_report* reports);
 
 /* ---- work plan of the step kernels (host only) ----
- * How the fused step (Algorithm 1 over the whole lattice) is split into
- * blocks for a lattice with the given parameters and objects (as
+ * How the marching kernels split the fused step (Algorithm 1 over the whole
+ * lattice) into blocks (small lattices step in bricks instead, one thread per
+ * site and one brick per block, and take from this plan only which FP32 planes
+ * use the bulk form of the force) for a lattice with the given parameters and objects (as
  * lq_set_boundaries would rasterize them, without records or extra object
  * sites) on a device that keeps `resident` step blocks resident at once
  * (> 0).  A chunk is the X x Y column tile whose first site is (x0, y0), over

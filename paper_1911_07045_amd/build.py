@@ -19,6 +19,7 @@ DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-pa
           "-ffp-contract=on"]
 SOURCES = [
     ("kernels.hip", DEVICE),
+    ("brick.hip", DEVICE),
     ("noalloc.hip", DEVICE),
     ("stream_copy.hip", DEVICE),
     ("abi.cpp", []),

@@ -463,6 +463,101 @@ static void plan_chunks(const lq_params& p, bool l23, int wide, const std::vecto
     }
 }
 
+// Brick of the kernels for small lattices.
+static void brick_size(bool l23, int64_t S[3]) {
+    S[0] = l23 ? Brick<true>::X : Brick<false>::X;
+    S[1] = l23 ? Brick<true>::Y : Brick<false>::Y;
+    S[2] = l23 ? Brick<true>::Z : Brick<false>::Z;
+}
+
+// Small lattices step in bricks (brick.hip).  A marching block waits for memory
+// once per plane, a brick once per step, so bricks win while a step is bound by
+// waits rather than by bytes: us per step, march against brick, one-constant
+// FP64 32^3 15.9 and 8.6, 64^3 29.6 and 17.1, 96^3 59.7 and 53.3.  A brick loads
+// its halo again (1.9 sites per site, 2.5 with L2/L3), which the Infinity Cache
+// serves while both state buffers fit in it (2 x 15 values per site, 256 MiB):
+// 112^3 FP64 83.5 and 102, 128^3 FP32 64.6 and 73.0.  The L2/L3/L4 kernels load
+// the whole shell and cross earlier.  Marching tiles that hang over the box's
+// edge cost their full width, so the limits hold for the share of the tiles
+// that lies in the box (at least 0.6), within the cache's 1.0 M sites in FP64 and
+// 1.9 M in FP32 (134x96x94 FP64: 99 and 111).  Where they were drawn, march against
+// brick: FP64 L1 128x128x60 59.5 and 62.7 (64x128x64 36.3 and 32.2), L2/L3
+// 128x64x80 50.5 and 54.6 (128x64x64 45.0 and 43.7), L4 64x128x64 51.3 and 53.2
+// (64x80x64 40.1 and 34.4); FP32 L1 112^3 57.0 and 48.0, L2/L3 128x50x60 23.4
+// and 24.4 (64x80x64 22.5 and 19.3).  Boxes that leave more than half of their
+// bricks' sites empty march, unless all of their bricks run at once.
+static bool bricks_for(const lq_params& p, bool l23) {
+    const double N = (double)p.n[0] * (double)p.n[1] * (double)p.n[2];
+    const double most = p.prec == LQ_F64 ? (p.L4 != 0.0 ? 4.0e5 : l23 ? 5.3e5 : 9.0e5) : (l23 ? 3.4e5 : 1.25e6);
+    int64_t S[3], nb = 1;
+    brick_size(l23, S);
+    for (int k = 0; k < 3; ++k) nb *= (p.n[k] + S[k] - 1) / S[k];
+    const int wide = tile_wide_for(p.n[0], p.prec, l23);
+    const int64_t TX = tile_x(p.prec, l23, wide), TY = tile_y(p.prec, l23, wide);
+    const double marched = (double)((p.n[0] + TX - 1) / TX * TX) * (double)((p.n[1] + TY - 1) / TY * TY) * (double)p.n[2];
+    return N <= (p.prec == LQ_F64 ? 1.0e6 : 1.9e6) && N * std::max(0.6, N / marched) <= most && (nb <= 256 || 2.0 * N >= (double)(nb * S[0] * S[1] * S[2]));
+}
+
+// The bricks of a lattice, x fastest: bit z of a brick's byte is set when the
+// sites of its plane z take the bulk form of the force.  FP64: when the padded
+// planes z - 1 .. z + 1 are all full bulk sites.  FP32: when the marching plan
+// gives them the bulk form (its tiles are wider, so fewer planes do).  The two
+// forms round differently and FP32 rounding grows along a relaxation; this way
+// an FP32 trajectory does not depend on the family of kernels that steps it.
+static std::vector<uint8_t> plan_bricks(const lq_params& p, bool l23, const std::vector<uint8_t>& mask, int device) {
+    int64_t S[3], nb[3];
+    brick_size(l23, S);
+    for (int k = 0; k < 3; ++k) nb[k] = (p.n[k] + S[k] - 1) / S[k];
+    std::vector<uint8_t> bits((size_t)(nb[0] * nb[1] * nb[2]), 0);
+    if (p.prec == LQ_F32) {
+        const int wide = tile_wide_for(p.n[0], p.prec, l23);
+        const int64_t TX = tile_x(p.prec, l23, wide), TY = tile_y(p.prec, l23, wide);
+        ChunkPlan plan;
+        plan_chunks(p, l23, wide, mask, resident_blocks(p, device, l23, wide), plan);
+        for (size_t i = 0; i < plan.chunks.size(); ++i) {
+            const Chunk& c = plan.chunks[i];
+            for (int64_t f = 0; f < c.zc; ++f) {
+                const bool bulk = plan.bulk[i] || (wide && ((plan.planes[i].w[f / 64] >> (f % 64)) & 1));
+                if (!bulk) continue;
+                const int64_t z = c.z0 + f;
+                for (int64_t by = c.y0 / S[1]; by < nb[1] && by * S[1] < c.y0 + TY; ++by)
+                    for (int64_t bx = c.x0 / S[0]; bx < nb[0] && bx * S[0] < c.x0 + TX; ++bx)
+                        bits[(size_t)(bx + nb[0] * (by + nb[1] * (z / S[2])))] |= (uint8_t)(1u << (z % S[2]));
+            }
+        }
+        return bits;
+    }
+    // padded coordinates of brick b along axis k; empty: the brick reaches off an open edge
+    auto padded = [&](int k, int64_t b) {
+        std::vector<int64_t> at;
+        for (int64_t i = b * S[k] - 1; i <= std::min((b + 1) * S[k], p.n[k]); ++i) {
+            if ((i < 0 || i >= p.n[k]) && !p.periodic[k]) return std::vector<int64_t>();
+            at.push_back((i + p.n[k]) % p.n[k]);
+        }
+        return at;
+    };
+    std::vector<uint8_t> full((size_t)p.n[2]);
+    for (int64_t by = 0; by < nb[1]; ++by)
+        for (int64_t bx = 0; bx < nb[0]; ++bx) {
+            const std::vector<int64_t> xs = padded(0, bx), ys = padded(1, by);
+            if (xs.empty() || ys.empty()) continue;
+            for (int64_t z = 0; z < p.n[2]; ++z) {
+                bool ok = true;
+                for (size_t y = 0; ok && y < ys.size(); ++y)
+                    for (size_t x = 0; ok && x < xs.size(); ++x)
+                        ok = mask[(size_t)(xs[x] + p.n[0] * (ys[y] + p.n[1] * z))] == M_FULL;
+                full[(size_t)z] = ok;
+            }
+            for (int64_t z = 0; z < p.n[2]; ++z) {
+                // no plane on an open z edge is full, so wrapping z is safe
+                const int64_t lo = (z + p.n[2] - 1) % p.n[2], hi = (z + 1) % p.n[2];
+                if (full[(size_t)lo] && full[(size_t)z] && full[(size_t)hi])
+                    bits[(size_t)(bx + nb[0] * (by + nb[1] * (z / S[2])))] |= (uint8_t)(1u << (z % S[2]));
+            }
+        }
+    return bits;
+}
+
 static void free_geometry(lq_lattice* lat) {
     if (lat->d_mask) (void)hipFree(lat->d_mask);
     if (lat->d_tile) (void)hipFree(lat->d_tile);
@@ -492,28 +587,37 @@ static int upload_geometry(lq_lattice* lat, const Geometry& g) {
     for (int k = 0; k < 3; ++k) d.per[k] = p.periodic[k];
     d.N = lat->N;
     d.A = p.A; d.B = p.B; d.C = p.C; d.L1 = p.L1; d.L2 = p.L2; d.L3 = p.L3; d.L4 = p.L4;
-    d.wide = tile_wide_for(p.n[0], p.prec, lat->l23);
     ChunkPlan plan;
-    d.two_waves = two_waves_for(p, lat->device, lat->l23, d.wide) ? 1 : 0;
-    plan_chunks(p, lat->l23, d.wide, g.mask, resident_blocks(p, lat->device, lat->l23, d.wide, d.two_waves != 0),
-                plan);
-    d.nchunks = (int)plan.chunks.size();
-    d.nblocks = (int)plan.first.size() - 1;
-    HIPCHK(lat, hipMalloc(&lat->d_first, plan.first.size() * sizeof(int32_t)));
-    HIPCHK(lat, hipMemcpy(lat->d_first, plan.first.data(), plan.first.size() * sizeof(int32_t),
-                          hipMemcpyHostToDevice));
-    const std::vector<uint8_t>& tiles = plan.bulk;
-    const std::vector<PlaneBits>& tile_planes = plan.planes;
-    HIPCHK(lat, hipMalloc(&lat->d_chunks, plan.chunks.size() * sizeof(Chunk)));
-    HIPCHK(lat, hipMemcpy(lat->d_chunks, plan.chunks.data(), plan.chunks.size() * sizeof(Chunk),
-                          hipMemcpyHostToDevice));
+    if (bricks_for(p, lat->l23)) {
+        int64_t S[3];
+        brick_size(lat->l23, S);
+        const uint64_t nbx = (uint64_t)((p.n[0] + S[0] - 1) / S[0]), nby = (uint64_t)((p.n[1] + S[1] - 1) / S[1]);
+        d.kind = KIND_BRICK;
+        d.two_waves = 0;
+        d.magic_x = ((uint64_t)1 << 32) / nbx + 1;
+        d.magic_xy = ((uint64_t)1 << 32) / (nbx * nby) + 1;
+        plan.bulk = plan_bricks(p, lat->l23, g.mask, lat->device);
+        d.nblocks = (int)plan.bulk.size();
+    } else {
+        d.kind = tile_wide_for(p.n[0], p.prec, lat->l23);
+        d.two_waves = two_waves_for(p, lat->device, lat->l23, d.kind) ? 1 : 0;
+        plan_chunks(p, lat->l23, d.kind, g.mask, resident_blocks(p, lat->device, lat->l23, d.kind, d.two_waves != 0),
+                    plan);
+        d.nblocks = (int)plan.first.size() - 1;
+        HIPCHK(lat, hipMalloc(&lat->d_first, plan.first.size() * sizeof(int32_t)));
+        HIPCHK(lat, hipMemcpy(lat->d_first, plan.first.data(), plan.first.size() * sizeof(int32_t),
+                              hipMemcpyHostToDevice));
+        HIPCHK(lat, hipMalloc(&lat->d_chunks, plan.chunks.size() * sizeof(Chunk)));
+        HIPCHK(lat, hipMemcpy(lat->d_chunks, plan.chunks.data(), plan.chunks.size() * sizeof(Chunk),
+                              hipMemcpyHostToDevice));
+        HIPCHK(lat, hipMalloc(&lat->d_tile_planes, plan.planes.size() * sizeof(PlaneBits)));
+        HIPCHK(lat, hipMemcpy(lat->d_tile_planes, plan.planes.data(), plan.planes.size() * sizeof(PlaneBits),
+                              hipMemcpyHostToDevice));
+    }
+    HIPCHK(lat, hipMalloc(&lat->d_tile, plan.bulk.size()));
+    HIPCHK(lat, hipMemcpy(lat->d_tile, plan.bulk.data(), plan.bulk.size(), hipMemcpyHostToDevice));
     HIPCHK(lat, hipMalloc(&lat->d_mask, (size_t)lat->N));
     HIPCHK(lat, hipMemcpy(lat->d_mask, g.mask.data(), (size_t)lat->N, hipMemcpyHostToDevice));
-    HIPCHK(lat, hipMalloc(&lat->d_tile, tiles.size()));
-    HIPCHK(lat, hipMemcpy(lat->d_tile, tiles.data(), tiles.size(), hipMemcpyHostToDevice));
-    HIPCHK(lat, hipMalloc(&lat->d_tile_planes, tile_planes.size() * sizeof(PlaneBits)));
-    HIPCHK(lat, hipMemcpy(lat->d_tile_planes, tile_planes.data(), tile_planes.size() * sizeof(PlaneBits),
-                          hipMemcpyHostToDevice));
     lat->n_anch = (int)g.anch_site.size();
     if (lat->n_anch > 0) {
         // dense per-site row index (1-based; 0 = no anchoring)
@@ -788,14 +892,12 @@ static int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 // Workspace: the second buffer of q, v and F; two slots of block partials
 // (step k writes slot k & 1 while step k + 1 reads it); the controller
 // state st[2] and its DcCtl word.
-static int64_t partials_bytes(const lq_lattice* lat) {
-    return align256(2 * partial_slots(lat) * 4 * (int64_t)sizeof(double));
-}
+static int64_t partials_bytes(int64_t slots) { return align256(2 * slots * 4 * (int64_t)sizeof(double)); }
 
 int64_t lq_workspace_bytes(const lq_lattice* lat) {
     if (!lat) return -1;
     const int64_t field = align256(5 * lat->N * (int64_t)elem_size(lat));
-    return 3 * field + partials_bytes(lat) + align256(2 * (int64_t)sizeof(FireDev) + (int64_t)sizeof(DcCtl));
+    return 3 * field + partials_bytes(partial_slots(lat)) + align256(2 * (int64_t)sizeof(FireDev) + (int64_t)sizeof(DcCtl));
 }
 
 static int check_fire_params(lq_lattice* lat, const lq_fire_params* fp) {
@@ -828,7 +930,7 @@ static int bind_buffers(lq_lattice* lat, void* q, void* v, void* F, void* worksp
     void* v1 = ws + field;
     void* F1 = ws + 2 * field;
     lat->d_partials = (double*)(ws + 3 * field);
-    lat->d_state = (FireDev*)(ws + 3 * field + partials_bytes(lat));
+    lat->d_state = (FireDev*)(ws + 3 * field + partials_bytes(partial_slots(lat)));
     lat->q = q;
     lat->v = v;
     lat->F = F;
@@ -1018,7 +1120,10 @@ int lq_minimize_noalloc(lq_lattice* lat, const lq_fire_params* fp, void* q, void
                         lq_min_result* out) {
     if (!lat) return fail(nullptr, LQ_EINVAL, "lattice is NULL");
     lat->bound = false;
-    const int64_t need = lq_workspace_bytes(lat);
+    // the limit counts one partial-sum slot per 256 sites (lattices in bricks
+    // may hold more; the array has room for them on top of its size)
+    const int64_t need = lq_workspace_bytes(lat) - partials_bytes(partial_slots(lat)) +
+                         partials_bytes(lat->dev.kind == KIND_BRICK ? n_energy_blocks(lat->dev) : partial_slots(lat));
     if (need > LQ_NOALLOC_WORKSPACE_BYTES) {
         char msg[192];
         std::snprintf(msg, sizeof msg,
@@ -1031,7 +1136,7 @@ int lq_minimize_noalloc(lq_lattice* lat, const lq_fire_params* fp, void* q, void
     void* ws = nullptr;
     int rc = noalloc_workspace(lat->device, &ws);
     if (rc != LQ_OK) return fail(lat, rc, "device address of the fixed workspace not available");
-    rc = lq_fire_init(lat, fp, q, v, F, ws, LQ_NOALLOC_WORKSPACE_BYTES, nullptr);
+    rc = lq_fire_init(lat, fp, q, v, F, ws, NOALLOC_ARRAY_BYTES, nullptr);
     if (rc == LQ_OK) rc = run_to_stop(lat, fp->max_steps, out);
     // the next call on this GPU may reuse the array: nothing may continue from it
     lat->bound = false;
@@ -1071,11 +1176,11 @@ struct lq_batch {
     int prec = -1;
     bool l23 = false;
     MemberDev* d_mem = nullptr;
-    int* d_tile_off = nullptr;   // narrow group's offsets, then the wide group's
+    int* d_tile_off = nullptr;   // per kind of step kernel its offsets
     int* d_fin_off = nullptr;
     FireDev* d_gather = nullptr;
     MemberDev* h_mem = nullptr;  // pinned, device order: narrow-tile members first
-    int* h_off = nullptr;        // pinned: tile offsets (capacity + 2), then finalize offsets (capacity + 1)
+    int* h_off = nullptr;        // pinned: block offsets (capacity + N_KINDS), then finalize offsets (capacity + 1)
     FireDev* h_gather = nullptr; // pinned, device order
     std::vector<int> order;      // device order -> index in members
 };
@@ -1112,11 +1217,11 @@ int lq_batch_create(int32_t capacity, void* stream, lq_batch** out) {
     b->stream = (hipStream_t)stream;
     hipError_t e = hipGetDevice(&b->device);
     if (e == hipSuccess) e = hipMalloc(&b->d_mem, sizeof(MemberDev) * capacity);
-    if (e == hipSuccess) e = hipMalloc(&b->d_tile_off, sizeof(int) * (capacity + 2));
+    if (e == hipSuccess) e = hipMalloc(&b->d_tile_off, sizeof(int) * (capacity + N_KINDS));
     if (e == hipSuccess) e = hipMalloc(&b->d_fin_off, sizeof(int) * (capacity + 1));
     if (e == hipSuccess) e = hipMalloc(&b->d_gather, sizeof(FireDev) * capacity);
     if (e == hipSuccess) e = hipHostMalloc(&b->h_mem, sizeof(MemberDev) * capacity, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc(&b->h_off, sizeof(int) * (2 * capacity + 3), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&b->h_off, sizeof(int) * (2 * capacity + N_KINDS + 1), hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc(&b->h_gather, sizeof(FireDev) * capacity, hipHostMallocDefault);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -1188,48 +1293,47 @@ int lq_batch_step(lq_batch* b, int64_t n_steps, lq_fire_report* reports) {
         if (!m->bound) return fail(nullptr, LQ_ESTATE, "a member lost its FIRE binding; remove it or bind it again");
     // the descriptors are rebuilt on every call (a few hundred bytes per
     // member), so members re-bound by lq_fire_init are picked up.  Members
-    // on narrow tiles come first and run in one launch per step, members on
-    // wide tiles in a second one.
+    // are ordered by kind of step kernel; each kind runs in one launch per step.
     b->order.clear();
-    for (int w = 0; w < 2; ++w)
+    BatchGroup group[N_KINDS] = {};
+    for (int g = 0; g < N_KINDS; ++g)
         for (int i = 0; i < n; ++i)
-            if (b->members[i]->dev.wide == w) b->order.push_back(i);
-    int n_narrow = 0;
-    while (n_narrow < n && !b->members[b->order[n_narrow]]->dev.wide) ++n_narrow;
-    const int n_wide = n - n_narrow;
-    int* tile_off = b->h_off;                     // narrow: [0, n_narrow], wide: [n_narrow + 1, n + 1]
-    int* fin_off = b->h_off + (b->capacity + 2);  // [0, n]
-    int tiles[2] = {0, 0}, f = 0;
-    for (int j = 0; j < n; ++j) {
-        lq_lattice* m = b->members[b->order[j]];
-        const int grp = j < n_narrow ? 0 : 1;
-        MemberDev& d = b->h_mem[j];
-        std::memset(&d, 0, sizeof(d));
-        d.L = m->dev;
-        const Bufs<double>& bb = m->b64;
-        for (int k = 0; k < 2; ++k) {
-            d.q[k] = bb.q[k];
-            d.v[k] = bb.v[k];
-            d.F[k] = bb.F[k];
+            if (b->members[i]->dev.kind == g) {
+                b->order.push_back(i);
+                ++group[g].n;
+            }
+    int* tile_off = b->h_off;                           // per kind its members + 1 offsets
+    int* fin_off = b->h_off + (b->capacity + N_KINDS);  // [0, n]
+    int f = 0;
+    for (int j = 0, g = 0, at = 0; g < N_KINDS; ++g) {
+        group[g].off = b->d_tile_off + at;
+        for (int i = 0; i < group[g].n; ++i, ++j) {
+            lq_lattice* m = b->members[b->order[j]];
+            MemberDev& d = b->h_mem[j];
+            std::memset(&d, 0, sizeof(d));
+            d.L = m->dev;
+            const Bufs<double>& bb = m->b64;
+            for (int k = 0; k < 2; ++k) {
+                d.q[k] = bb.q[k];
+                d.v[k] = bb.v[k];
+                d.F[k] = bb.F[k];
+            }
+            d.partials = m->d_partials;
+            d.st = m->d_state;
+            d.nblocks = (int)n_step_blocks(m->dev);
+            tile_off[at++] = group[g].blocks;
+            fin_off[j] = f;
+            group[g].blocks += d.nblocks;
+            f += fin_blocks_of(m);
         }
-        d.partials = m->d_partials;
-        d.st = m->d_state;
-        d.nblocks = (int)n_step_blocks(m->dev);
-        tile_off[grp == 0 ? j : j + 1] = tiles[grp];
-        fin_off[j] = f;
-        tiles[grp] += d.nblocks;
-        f += fin_blocks_of(m);
+        tile_off[at++] = group[g].blocks;
     }
-    tile_off[n_narrow] = tiles[0];
-    tile_off[n + 1] = tiles[1];
     fin_off[n] = f;
     HIPCHK(nullptr, hipMemcpyAsync(b->d_mem, b->h_mem, sizeof(MemberDev) * n, hipMemcpyHostToDevice, b->stream));
-    HIPCHK(nullptr, hipMemcpyAsync(b->d_tile_off, tile_off, sizeof(int) * (n + 2), hipMemcpyHostToDevice,
+    HIPCHK(nullptr, hipMemcpyAsync(b->d_tile_off, tile_off, sizeof(int) * (n + N_KINDS), hipMemcpyHostToDevice,
                                    b->stream));
     HIPCHK(nullptr, hipMemcpyAsync(b->d_fin_off, fin_off, sizeof(int) * (n + 1), hipMemcpyHostToDevice, b->stream));
-    int rc = launch_batch_steps(b->prec, b->l23, b->d_mem, n_narrow, b->d_tile_off, tiles[0], n_wide,
-                                b->d_tile_off + n_narrow + 1, tiles[1], b->d_fin_off, f, b->d_gather, n_steps,
-                                b->stream);
+    int rc = launch_batch_steps(b->prec, b->l23, b->d_mem, group, b->d_fin_off, f, b->d_gather, n_steps, b->stream);
     if (rc != LQ_OK) return fail(nullptr, rc, "batch kernel launch failed");
     HIPCHK(nullptr, hipMemcpyAsync(b->h_gather, b->d_gather, sizeof(FireDev) * n, hipMemcpyDeviceToHost, b->stream));
     HIPCHK(nullptr, hipStreamSynchronize(b->stream));

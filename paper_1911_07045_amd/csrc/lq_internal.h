@@ -1,6 +1,7 @@
 // Internal declarations shared by the host side of liblqfire and its kernels.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include <string>
@@ -104,6 +105,21 @@ struct Tile<float, L23, 0> : TileGeom<64, 8, Tile<float, L23, 1>::WAVES> {};
 template <bool L23>
 struct Tile<double, L23, 0> : TileGeom<32, 8, Tile<double, L23, 1>::WAVES> {};
 
+// Brick geometry of the kernels for small lattices (brick.hip): a block of
+// X x Y x Z threads owns one brick, one site per thread.  HALO counts the sites
+// of the one-site shell that the stencil reads (L2/L3/L4: the whole shell), IPT
+// the shell sites a thread loads.  One-constant kernels take 16 x 8 x 4 (512
+// threads; 448 halo sites, one per thread), the others, whose registers allow
+// three waves per SIMD, 16 x 4 x 4: three blocks of 256 threads per compute
+// unit instead of one of 512.
+template <bool L23>
+struct Brick {
+    static constexpr int X = 16, Y = L23 ? 4 : 8, Z = 4, N = X * Y * Z;
+    static constexpr int PX = X + 2, PY = Y + 2, PZ = Z + 2;
+    static constexpr int HALO = L23 ? PX * PY * PZ - N : 2 * (X * Y + X * Z + Y * Z);
+    static constexpr int IPT = (HALO + N - 1) / N;
+};
+
 template <int W>
 inline int tile_x_w(int prec, bool l23) {
     if (prec == LQ_F64) return l23 ? Tile<double, true, W>::X : Tile<double, false, W>::X;
@@ -117,6 +133,12 @@ inline int tile_y_w(int prec, bool l23) {
 inline int tile_x(int prec, bool l23, int wide) { return wide ? tile_x_w<1>(prec, l23) : tile_x_w<0>(prec, l23); }
 inline int tile_y(int prec, bool l23, int wide) { return wide ? tile_y_w<1>(prec, l23) : tile_y_w<0>(prec, l23); }
 inline int tile_threads(int prec, bool l23, int wide) { return tile_x(prec, l23, wide) * tile_y(prec, l23, wide); }
+inline int brick_threads(bool l23) { return l23 ? Brick<true>::N : Brick<false>::N; }
+// kinds of step kernel: marching tiles (narrow, wide) and bricks
+enum : int { KIND_NARROW = 0, KIND_WIDE = 1, KIND_BRICK = 2, N_KINDS = 3 };
+inline int step_threads(int prec, bool l23, int kind) {
+    return kind == KIND_BRICK ? brick_threads(l23) : tile_threads(prec, l23, kind);
+}
 // a lattice narrower than one wide tile takes the narrow one
 inline int tile_wide_for(int64_t nx, int prec, bool l23) { return nx >= tile_x_w<1>(prec, l23) ? 1 : 0; }
 
@@ -141,7 +163,8 @@ struct LatDev {
     const uint8_t* mask;
     const Chunk* chunks;       // of the step kernels, in block order
     const int32_t* first;      // block b of the step kernels marches chunks first[b] .. first[b + 1] - 1
-    const uint8_t* tile_bulk;  // per chunk, 1: every site of the padded tile has mask M_FULL
+    const uint8_t* tile_bulk;  // per chunk, 1: every site of the padded tile has mask M_FULL;
+                               // per brick, bit z: its plane z takes the bulk form
     const PlaneBits* tile_planes;  // per chunk
     int n_anch;
     const int32_t* anch_index;  // per site: 1 + row of anch_data, 0 when not anchored
@@ -149,9 +172,9 @@ struct LatDev {
     const void* anch_force;     // ANCH_FSTRIDE per anchored site, element type of the field
     double ext[5];              // constant external-field force per simulated site
     double A, B, C, L1, L2, L3, L4;
-    int nchunks;  // chunks of one step launch
     int nblocks;  // blocks of one step launch
-    int wide;     // tile width kind of the step kernels (1 wide, 0 narrow)
+    int kind;     // KIND_* of the step kernels
+    uint64_t magic_x, magic_xy;  // bricks: 2^32 / d + 1 for d = bricks per row and per plane
     int two_waves;  // FP64 L2/L3 wide: the step kernels held to two waves per SIMD
 };
 
@@ -225,11 +248,20 @@ int launch_energy(const LatDev& L, bool l23, int prec, const void* q, double* pa
                   EnergyOut* out, uint32_t* ticket, void* stream);
 int launch_uniaxial(const LatDev& L, int prec, const double* dirs, double S, void* q,
                     void* stream);
-// Members [0, n_narrow) of mem use narrow tiles, the next n_wide wide ones;
-// tile_off / tile_off_wide hold each group's cumulative tile offsets.
-int launch_batch_steps(int prec, bool l23, const MemberDev* mem, int n_narrow, const int* tile_off,
-                       int tiles_narrow, int n_wide, const int* tile_off_wide, int tiles_wide,
+// The members of mem are ordered by kind of step kernel; group[kind] holds
+// their number, their blocks and the cumulative block offsets of the kind.
+struct BatchGroup {
+    int n, blocks;
+    const int* off;
+};
+int launch_batch_steps(int prec, bool l23, const MemberDev* mem, const BatchGroup group[N_KINDS],
                        const int* fin_off, int total_fin, FireDev* gather, int64_t n_steps, void* stream);
+// Brick kernels (brick.hip).
+void launch_brick_forces(const LatDev& L, bool l23, int prec, const void* q, void* F, void* stream);
+void launch_brick_step(const LatDev& L, bool l23, int prec, int method, const void* bufs, double* partials,
+                       FireDev* st, int k, void* stream);
+void launch_brick_batch(bool l23, int prec, const MemberDev* mem, const int* off, int n, int bricks, int k,
+                        void* stream);
 int64_t n_step_blocks(const LatDev& L);
 int step_blocks_per_cu(int prec, bool l23, bool l4, int wide, bool two);
 int64_t n_energy_blocks(const LatDev& L);
