@@ -20,6 +20,7 @@ DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-pa
 SOURCES = [
     ("kernels.hip", DEVICE),
     ("brick.hip", DEVICE),
+    ("observe.hip", DEVICE),
     ("noalloc.hip", DEVICE),
     ("stream_copy.hip", DEVICE),
     ("abi.cpp", []),
@@ -38,7 +39,7 @@ def _compile(src, extra):
 
 def build() -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=5) as ex:
+    with cf.ThreadPoolExecutor(max_workers=7) as ex:
         objs = list(ex.map(lambda s: _compile(*s), SOURCES))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs

@@ -1,7 +1,7 @@
 // Host side of liblqfire: the extern "C" entry points of lqfire.h.
 //
 // The handle owns the geometry tables on the device (neighbour masks, tile
-// flags, anchoring sums) and small scratch for the energy sum.  The caller
+// flags, anchoring sums) and small scratch for the energy sum and defect count.  The caller
 // owns every field buffer and the FIRE workspace.
 #include <hip/hip_runtime.h>
 
@@ -41,12 +41,11 @@ struct lq_lattice {
     double* d_anch_data = nullptr;
     void* d_anch_force = nullptr;  // K upper triangle and b of each row, in the field's element type
     int n_anch = 0;
-    // energy scratch
-    double* d_epart = nullptr;
-    EnergyOut* d_eout = nullptr;
-    uint32_t* d_eticket = nullptr;
-    EnergyOut* h_eout = nullptr;  // pinned
-    unsigned long long* h_count = nullptr;  // pinned: defect count
+    // energy and defect count: scratch, and pinned results that the kernels
+    // write through their device addresses
+    void* d_observe = nullptr;
+    EnergyOut *h_eout = nullptr, *d_eout = nullptr;
+    unsigned long long *h_count = nullptr, *d_count = nullptr;
     // minimizer binding
     bool bound = false;
     int method = LQ_METHOD_FIRE;
@@ -683,14 +682,12 @@ int lq_lattice_create(const lq_params* p, void* stream, lq_lattice** out) {
     rc = rasterize(lat->p, lat->S0, nullptr, 0, nullptr, 0, nullptr, 0, g, err);
     if (rc == LQ_OK) rc = upload_geometry(lat, g);
     if (rc == LQ_OK) {
-        const int64_t nb = std::max<int64_t>(n_energy_blocks(lat->dev), 1);
-        if (hipMalloc(&lat->d_epart, (size_t)nb * 4 * sizeof(double)) != hipSuccess ||
-            hipMalloc(&lat->d_eout, sizeof(EnergyOut)) != hipSuccess ||
-            hipMalloc(&lat->d_eticket, 256) != hipSuccess ||
+        if (hipMalloc(&lat->d_observe, (size_t)n_observe_bytes(lat->dev)) != hipSuccess ||
             hipHostMalloc(&lat->h_eout, sizeof(EnergyOut), hipHostMallocDefault) != hipSuccess ||
+            hipHostGetDevicePointer((void**)&lat->d_eout, lat->h_eout, 0) != hipSuccess ||
             hipHostMalloc(&lat->h_state, sizeof(FireDev), hipHostMallocDefault) != hipSuccess ||
             hipHostMalloc(&lat->h_count, sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess ||
-            hipMemset(lat->d_eticket, 0, 256) != hipSuccess) {
+            hipHostGetDevicePointer((void**)&lat->d_count, lat->h_count, 0) != hipSuccess) {
             (void)hipGetLastError();
             err = "device allocation failed";
             rc = LQ_ENOMEM;
@@ -712,9 +709,7 @@ int lq_lattice_destroy(lq_lattice* lat) {
     (void)hipSetDevice(lat->device);
     (void)hipStreamSynchronize(lat->stream);
     free_geometry(lat);
-    if (lat->d_epart) (void)hipFree(lat->d_epart);
-    if (lat->d_eout) (void)hipFree(lat->d_eout);
-    if (lat->d_eticket) (void)hipFree(lat->d_eticket);
+    if (lat->d_observe) (void)hipFree(lat->d_observe);
     if (lat->h_eout) (void)hipHostFree(lat->h_eout);
     if (lat->h_count) (void)hipHostFree(lat->h_count);
     if (lat->h_state) (void)hipHostFree(lat->h_state);
@@ -844,10 +839,8 @@ int lq_energy(lq_lattice* lat, const void* q, lq_energy_terms* out) {
     int rc = check_dev_ptr(lat, q, "q");
     if (rc != LQ_OK) return rc;
     HIPCHK(lat, hipSetDevice(lat->device));
-    rc = launch_energy(lat->dev, lat->l23, lat->p.prec, q, lat->d_epart, lat->d_eout, lat->d_eticket,
-                       lat->stream);
+    rc = launch_energy(lat->dev, lat->l23, lat->p.prec, q, (double*)lat->d_observe, lat->d_eout, lat->stream);
     if (rc != LQ_OK) return fail(lat, rc, "kernel launch failed");
-    HIPCHK(lat, hipMemcpyAsync(lat->h_eout, lat->d_eout, sizeof(EnergyOut), hipMemcpyDeviceToHost, lat->stream));
     HIPCHK(lat, hipStreamSynchronize(lat->stream));
     out->bulk = lat->h_eout->bulk;
     out->elastic = lat->h_eout->elastic;
@@ -870,13 +863,10 @@ int lq_director_field(lq_lattice* lat, const void* q, void* dirs, void* lambda_m
     if (q == dirs || q == lambda_max || (dirs && dirs == lambda_max))
         return fail(lat, LQ_EINVAL, "outputs must not alias q or each other");
     HIPCHK(lat, hipSetDevice(lat->device));
-    // the defect counter sits in the energy kernel's ticket block, past the ticket
-    unsigned long long* d_count = n_defects ? (unsigned long long*)((char*)lat->d_eticket + 128) : nullptr;
-    rc = launch_directors(lat->dev, lat->p.prec, q, dirs, lambda_max, defect, threshold, d_count, lat->stream);
+    rc = launch_directors(lat->dev, lat->p.prec, q, dirs, lambda_max, defect, threshold, (uint32_t*)lat->d_observe,
+                          n_defects ? lat->d_count : nullptr, lat->stream);
     if (rc != LQ_OK) return fail(lat, rc, "kernel launch failed");
     if (n_defects) {
-        HIPCHK(lat, hipMemcpyAsync(lat->h_count, d_count, sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                                   lat->stream));
         HIPCHK(lat, hipStreamSynchronize(lat->stream));
         *n_defects = (int64_t)*lat->h_count;
     }
@@ -993,7 +983,6 @@ int lq_fire_init(lq_lattice* lat, const lq_fire_params* fp, void* q, void* v, vo
     s.tol = fp->force_tol;
     s.n_min = fp->n_min;
     s.max_steps = fp->max_steps;
-    s.ticket = 0;
     s.method = LQ_METHOD_FIRE;
     return start_controller(lat, s, v);
 }

@@ -24,8 +24,8 @@
 // kick and the drift to every site it needs (its tile plus a one-site halo,
 // recomputed in LDS), evaluates the force at the new positions, applies the
 // second half kick and writes q, v, F to the other buffer.  Per-block FP64
-// partial sums of F.v, |F|^2, |v|^2 and max|F_i| are combined by the last
-// block to finish (atomic ticket), which then runs the controller.  The host
+// partial sums of F.v, |F|^2, |v|^2 and max|F_i| are combined at the start of
+// the next step kernel, every block of which runs the controller.  The host
 // never waits between steps.  The same march runs gradient descent and
 // Nesterov's accelerated gradient (a compile-time mode) and the force alone.
 // Further kernels: the energy (FP64 per-term sums), the uniaxial initial
@@ -42,41 +42,6 @@
 #include "lq_site.h"
 
 namespace lq {
-
-// Writes this block's partials, and in the last block to arrive reduces all
-// of them in block order and runs the controller (the reduction of the FIRE
-// initialisation; the step kernels run theirs at the next kernel's start).
-__device__ void grid_finish(double r[4], double* partials, FireDev* st, int nblocks, int bid,
-                            double (*scratch)[4], int* flag) {
-    block_reduce4(r, scratch);
-    if (threadIdx.x == 0) {
-        double* p = partials + 4 * (int64_t)bid;
-        p[0] = r[0]; p[1] = r[1]; p[2] = r[2]; p[3] = r[3];
-        __threadfence();
-        unsigned t = atomicAdd(&st->ticket, 1u);
-        *flag = (t == (unsigned)(nblocks - 1));
-    }
-    __syncthreads();
-    if (!*flag) return;
-    __threadfence();
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-        const volatile double* p = partials + 4 * (int64_t)b;
-        s[0] += p[0]; s[1] += p[1]; s[2] += p[2]; s[3] = fmax(s[3], p[3]);
-    }
-    __syncthreads();
-    block_reduce4(s, scratch);
-    if (threadIdx.x == 0) {
-        // the controller on a register copy of the state: one round trip to
-        // read it and one to write it, instead of a chain of dependent
-        // global reads (no other block touches the state any more)
-        FireDev c = *st;
-        fire_control(&c, s[0], s[1], s[2], s[3]);
-        c.ticket = 0;
-        *st = c;
-        __threadfence();
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Stencil view used by the force: offsets (dx, dy, dz) in {-1, 0, 1} around
@@ -574,7 +539,7 @@ __global__ __launch_bounds__((Tile<T, L23, W>::N)) __attribute__((amdgpu_waves_p
 // ---------------------------------------------------------------------------
 // Batched steps: one launch advances every member of a batch of lattices by
 // one FIRE step.  Block b belongs to the member m with off[m] <= b <
-// off[m+1]; each member keeps its own controller, partials and ticket, so
+// off[m+1]; each member keeps its own controller and partials, so
 // its trajectory is bit for bit the one it has alone.
 template <typename T, bool L23, int W>
 __global__ __launch_bounds__((Tile<T, L23, W>::N)) __attribute__((amdgpu_waves_per_eu(Tile<T, L23, W>::WAVES))) void k_march_batch(const MemberDev* __restrict__ mem,
@@ -638,13 +603,13 @@ __global__ void k_batch_reset_gather(const MemberDev* __restrict__ mem, int n_me
 }
 
 // ---------------------------------------------------------------------------
-// lq_fire_init reduction: |F|^2, |v|^2, F.v, max|F_i| of the initial state,
-// then the controller's initial convergence test.
+// lq_fire_init reduction: block partials of |F|^2, |v|^2, F.v, max|F_i| of the
+// initial state; then one block sums them in block order and runs the
+// controller's initial convergence test.
 template <typename T>
 __global__ __launch_bounds__(256) void k_init_reduce(const T* __restrict__ F, const T* __restrict__ v,
-                                                     int64_t n, double* partials, FireDev* st) {
+                                                     int64_t n, double* partials) {
     __shared__ double scratch[4][4];
-    __shared__ int last_flag;
     double r[4] = {0.0, 0.0, 0.0, 0.0};
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
@@ -655,7 +620,22 @@ __global__ __launch_bounds__(256) void k_init_reduce(const T* __restrict__ F, co
         r[3] = fmax(r[3], fabs(f));
         if (f != f) r[3] = f;
     }
-    grid_finish(r, partials, st, (int)gridDim.x, (int)blockIdx.x, scratch, &last_flag);
+    block_reduce4(r, scratch);
+    if (threadIdx.x == 0) {
+        double* p = partials + 4 * (int64_t)blockIdx.x;
+        p[0] = r[0]; p[1] = r[1]; p[2] = r[2]; p[3] = r[3];
+    }
+}
+
+__global__ __launch_bounds__(256) void k_init_control(const double* partials, int nblocks, FireDev* st) {
+    __shared__ double scratch[4][4];
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    sum_partials(partials, nblocks, s, scratch);
+    if (threadIdx.x == 0) {
+        FireDev c = *st;
+        fire_control(&c, s[0], s[1], s[2], s[3]);
+        *st = c;
+    }
 }
 
 __global__ void k_begin(FireDev* st, int64_t n_steps) {
@@ -729,226 +709,6 @@ __global__ __launch_bounds__(256) void k_uniaxial(LatDev L, const double* __rest
             r[4] = h * ny * nz;
         }
         for (int c = 0; c < 5; ++c) q[c * N + s] = T(r[c]);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Energy: one thread per site, FP64 arithmetic, per-term block partials
-// reduced in block order by the last block.
-template <typename T, bool L23>
-__global__ __launch_bounds__(256) void k_energy(LatDev L, const T* __restrict__ q, double* partials,
-                                                EnergyOut* out, uint32_t* ticket) {
-    __shared__ double scratch[4][4];
-    __shared__ int last_flag;
-    const int64_t N = L.N;
-    double e_b = 0.0, e_d = 0.0, e_a = 0.0, e_x = 0.0;
-    for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < N;
-         s += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t m = L.mask[s];
-        if (!(m & M_SIM)) continue;
-        const int x = (int)(s % L.nx), y = (int)((s / L.nx) % L.ny), z = (int)(s / ((int64_t)L.nx * L.ny));
-        double q0[5];
-        for (int c = 0; c < 5; ++c) q0[c] = (double)q[c * N + s];
-        double Q[3][3];
-        full_of(q0, Q);
-        double t2 = 0.0, t3 = 0.0;
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) {
-                t2 += Q[i][j] * Q[j][i];
-                for (int k = 0; k < 3; ++k) t3 += Q[i][j] * Q[j][k] * Q[k][i];
-            }
-        e_b += 0.5 * L.A * t2 + L.B / 3.0 * t3 + 0.25 * L.C * t2 * t2;
-        // neighbour q along each axis and direction
-        double qn[3][2][5];
-        for (int k = 0; k < 3; ++k)
-            for (int si = 0; si < 2; ++si) {
-                const int sg = si == 0 ? 1 : -1;
-                for (int c = 0; c < 5; ++c) qn[k][si][c] = 0.0;
-                if (!has_nb(m, k, sg)) continue;
-                int c3[3] = {x, y, z};
-                const int n3[3] = {L.nx, L.ny, L.nz};
-                c3[k] = wrapc(c3[k] + sg, n3[k], L.per[k]);
-                const int64_t t = (int64_t)c3[0] + (int64_t)L.nx * ((int64_t)c3[1] + (int64_t)L.ny * c3[2]);
-                for (int c = 0; c < 5; ++c) qn[k][si][c] = (double)q[c * N + t];
-            }
-        double ed = 0.0;
-        double Cm[3][5];
-        for (int k = 0; k < 3; ++k) {
-            const int nk = n_choices(m, k);
-            double acc1 = 0.0, acc23 = 0.0;
-            for (int si = 0; si < 2; ++si) {
-                if (!has_nb(m, k, si == 0 ? 1 : -1)) continue;
-                double d[5], o[5];
-                for (int c = 0; c < 5; ++c) d[c] = qn[k][si][c] - q0[c];
-                metric(d, o);
-                for (int c = 0; c < 5; ++c) acc1 += d[c] * o[c];
-                if (L23) {
-                    column_metric(k, d, o);
-                    for (int c = 0; c < 5; ++c) acc23 += d[c] * o[c];
-                }
-            }
-            if (nk > 0) {
-                ed += 0.5 * L.L1 * acc1 / nk;
-                if (L23) ed += 0.5 * (L.L2 + L.L3) * acc23 / nk;
-            }
-            double ap, a0, am;
-            mean_diff_coef(m, k, ap, a0, am);
-            for (int c = 0; c < 5; ++c)
-                Cm[k][c] = ap * qn[k][0][c] + a0 * q0[c] + am * qn[k][1][c];
-        }
-        if (L23) {
-            // sum_{j<k} L2 sum_i C_j,ij C_k,ik + L3 sum_i C_j,ik C_k,ij
-            double Cf[3][3][3];
-            for (int k = 0; k < 3; ++k) full_of(Cm[k], Cf[k]);
-            for (int j = 0; j < 3; ++j)
-                for (int k = j + 1; k < 3; ++k)
-                    for (int i = 0; i < 3; ++i)
-                        ed += L.L2 * Cf[j][i][j] * Cf[k][i][k] + L.L3 * Cf[j][i][k] * Cf[k][i][j];
-            // chiral term L4/2 eps_lik Q_lj C_k,ij
-            double e4 = 0.0;
-            for (int l = 0; l < 3; ++l)
-                for (int i = 0; i < 3; ++i)
-                    for (int k = 0; k < 3; ++k) {
-                        if (eps3(l, i, k) == 0) continue;
-                        for (int j = 0; j < 3; ++j) e4 += eps3(l, i, k) * Q[l][j] * Cf[k][i][j];
-                    }
-            ed += 0.5 * L.L4 * e4;
-        }
-        e_d += ed;
-        double qe = 0.0;
-        for (int c = 0; c < 5; ++c) qe += L.ext[c] * q0[c];
-        e_x -= qe;
-        if (m & M_ANCH) {
-            const int at = L.anch_index[s] - 1;
-            if (at >= 0) {
-                // 1/2 q^T K q + b^T q + c
-                const double* d = L.anch_data + ANCH_STRIDE * (int64_t)at;
-                double quad = 0.0, lin = 0.0;
-                int t = 0;
-                for (int a = 0; a < 5; ++a) {
-                    lin += d[15 + a] * q0[a];
-                    for (int b = a; b < 5; ++b, ++t)
-                        quad += (b == a ? 0.5 : 1.0) * d[t] * q0[a] * q0[b];
-                }
-                e_a += quad + lin + d[20];
-            }
-        }
-    }
-    double r[4] = {e_b, e_d, e_a, e_x};
-    block_reduce4<false>(r, scratch);
-    if (threadIdx.x == 0) {
-        double* p = partials + 4 * (int64_t)blockIdx.x;
-        p[0] = r[0]; p[1] = r[1]; p[2] = r[2]; p[3] = r[3];
-        __threadfence();
-        unsigned t = atomicAdd(ticket, 1u);
-        last_flag = (t == gridDim.x - 1);
-    }
-    __syncthreads();
-    if (!last_flag) return;
-    __threadfence();
-    double s4[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x) {
-        const volatile double* p = partials + 4 * (int64_t)b;
-        s4[0] += p[0]; s4[1] += p[1]; s4[2] += p[2]; s4[3] += p[3];
-    }
-    __syncthreads();
-    block_reduce4<false>(s4, scratch);
-    if (threadIdx.x == 0) {
-        out->bulk = s4[0]; out->elastic = s4[1]; out->anch = s4[2]; out->ext = s4[3];
-        *ticket = 0;
-        __threadfence();
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Director and defect extraction (Eq. Qtensor and the text after it; the
-// display of directors and defects in sec. IV): per simulated site the
-// largest eigenvalue of Q and its eigenvector, and whether that eigenvalue
-// lies below a threshold.  FP64 arithmetic.  For a traceless symmetric Q
-// with p = sqrt(tr(Q^2)/6) the eigenvalues are 2p cos((acos(r) + 2 pi m)/3),
-// r = det(Q)/(2 p^3) (the trigonometric solution of the characteristic
-// cubic), m = 0 giving the largest.  The eigenvector is the largest cross
-// product of two rows of Q - lambda I; when Q - lambda I has rank one (the
-// largest eigenvalue is doubly degenerate) any vector normal to its
-// non-zero row is an eigenvector.  n and -n being equal, the sign makes the
-// largest-magnitude component positive.
-template <typename T>
-__global__ __launch_bounds__(256) void k_directors(LatDev L, const T* __restrict__ q, T* __restrict__ dirs,
-                                                   T* __restrict__ lmax, uint8_t* __restrict__ defect,
-                                                   double thr, unsigned long long* count) {
-    __shared__ unsigned int block_count;
-    if (threadIdx.x == 0) block_count = 0;
-    __syncthreads();
-    const int64_t N = L.N;
-    unsigned int mine = 0;
-    for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < N;
-         s += (int64_t)gridDim.x * blockDim.x) {
-        double n[3] = {0.0, 0.0, 0.0}, lam = 0.0;
-        const bool sim = (L.mask[s] & M_SIM) != 0;
-        if (sim) {
-            double v[5];
-            for (int c = 0; c < 5; ++c) v[c] = (double)q[c * N + s];
-            double Q[3][3];
-            full_of(v, Q);
-            double p2 = 0.0;
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < 3; ++j) p2 += Q[i][j] * Q[i][j];
-            if (p2 > 0.0) {
-                const double p = sqrt(p2 / 6.0);
-                const double det = Q[0][0] * (Q[1][1] * Q[2][2] - Q[1][2] * Q[2][1]) -
-                                   Q[0][1] * (Q[1][0] * Q[2][2] - Q[1][2] * Q[2][0]) +
-                                   Q[0][2] * (Q[1][0] * Q[2][1] - Q[1][1] * Q[2][0]);
-                const double r = fmin(1.0, fmax(-1.0, det / (2.0 * p * p * p)));
-                lam = 2.0 * p * cos(acos(r) / 3.0);
-                double A[3][3];
-                for (int i = 0; i < 3; ++i)
-                    for (int j = 0; j < 3; ++j) A[i][j] = Q[i][j] - (i == j ? lam : 0.0);
-                double best = -1.0;
-                for (int a = 0; a < 3; ++a)
-                    for (int b = a + 1; b < 3; ++b) {
-                        const double c[3] = {A[a][1] * A[b][2] - A[a][2] * A[b][1],
-                                             A[a][2] * A[b][0] - A[a][0] * A[b][2],
-                                             A[a][0] * A[b][1] - A[a][1] * A[b][0]};
-                        const double c2 = c[0] * c[0] + c[1] * c[1] + c[2] * c[2];
-                        if (c2 > best) { best = c2; n[0] = c[0]; n[1] = c[1]; n[2] = c[2]; }
-                    }
-                if (!(best > 0.0)) {
-                    // rank one: a vector normal to the largest row
-                    int a = 0;
-                    double rb = -1.0;
-                    for (int i = 0; i < 3; ++i) {
-                        const double r2 = A[i][0] * A[i][0] + A[i][1] * A[i][1] + A[i][2] * A[i][2];
-                        if (r2 > rb) { rb = r2; a = i; }
-                    }
-                    int e = 0;
-                    for (int k = 1; k < 3; ++k)
-                        if (fabs(A[a][k]) < fabs(A[a][e])) e = k;
-                    double u[3] = {0.0, 0.0, 0.0};
-                    u[e] = 1.0;
-                    n[0] = A[a][1] * u[2] - A[a][2] * u[1];
-                    n[1] = A[a][2] * u[0] - A[a][0] * u[2];
-                    n[2] = A[a][0] * u[1] - A[a][1] * u[0];
-                    best = n[0] * n[0] + n[1] * n[1] + n[2] * n[2];
-                }
-                const double inv = best > 0.0 ? 1.0 / sqrt(best) : 0.0;
-                int big = 0;
-                for (int k = 1; k < 3; ++k)
-                    if (fabs(n[k]) > fabs(n[big])) big = k;
-                const double sg = n[big] < 0.0 ? -inv : inv;
-                for (int k = 0; k < 3; ++k) n[k] *= sg;
-            }
-        }
-        const bool is_defect = sim && lam < thr;
-        mine += is_defect ? 1u : 0u;
-        if (dirs)
-            for (int k = 0; k < 3; ++k) dirs[k * N + s] = T(n[k]);
-        if (lmax) lmax[s] = T(lam);
-        if (defect) defect[s] = is_defect ? 1 : 0;
-    }
-    if (count) {
-        atomicAdd(&block_count, mine);
-        __syncthreads();
-        if (threadIdx.x == 0 && block_count) atomicAdd(count, (unsigned long long)block_count);
     }
 }
 
@@ -1084,38 +844,9 @@ int launch_lookahead(const LatDev& L, int prec, const void* q, const void* m, do
     return hip_status(hipGetLastError());
 }
 
-int launch_directors(const LatDev& L, int prec, const void* q, void* dirs, void* lmax, uint8_t* defect,
-                     double thr, unsigned long long* count, void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    if (count) {
-        k_fill_zero<<<1, 64, 0, s>>>((uint32_t*)count, 2);
-        if (hipGetLastError() != hipSuccess) return LQ_EHIP;
-    }
-    const int g = grid_1d(L.N);
-    if (prec == LQ_F64)
-        k_directors<double><<<g, 256, 0, s>>>(L, (const double*)q, (double*)dirs, (double*)lmax, defect, thr, count);
-    else
-        k_directors<float><<<g, 256, 0, s>>>(L, (const float*)q, (float*)dirs, (float*)lmax, defect, thr, count);
-    return hip_status(hipGetLastError());
-}
-
 int launch_fill_zero(void* p, int64_t bytes, void* stream) {
     const int64_t w = bytes / 4;
     k_fill_zero<<<grid_1d(w), 256, 0, (hipStream_t)stream>>>((uint32_t*)p, w);
-    return hip_status(hipGetLastError());
-}
-
-int launch_energy(const LatDev& L, bool l23, int prec, const void* q, double* partials,
-                  EnergyOut* out, uint32_t* ticket, void* stream) {
-    hipStream_t s = (hipStream_t)stream;
-    const int g = (int)n_energy_blocks(L);
-    if (prec == LQ_F64) {
-        if (l23) k_energy<double, true><<<g, 256, 0, s>>>(L, (const double*)q, partials, out, ticket);
-        else k_energy<double, false><<<g, 256, 0, s>>>(L, (const double*)q, partials, out, ticket);
-    } else {
-        if (l23) k_energy<float, true><<<g, 256, 0, s>>>(L, (const float*)q, partials, out, ticket);
-        else k_energy<float, false><<<g, 256, 0, s>>>(L, (const float*)q, partials, out, ticket);
-    }
     return hip_status(hipGetLastError());
 }
 
@@ -1182,8 +913,10 @@ int launch_fire_init_reduce(const LatDev& L, int prec, const void* F, const void
     hipStream_t s = (hipStream_t)stream;
     const int64_t n = 5 * L.N;
     const int g = (int)n_energy_blocks(L);
-    if (prec == LQ_F64) k_init_reduce<double><<<g, 256, 0, s>>>((const double*)F, (const double*)v, n, partials, st);
-    else k_init_reduce<float><<<g, 256, 0, s>>>((const float*)F, (const float*)v, n, partials, st);
+    if (prec == LQ_F64) k_init_reduce<double><<<g, 256, 0, s>>>((const double*)F, (const double*)v, n, partials);
+    else k_init_reduce<float><<<g, 256, 0, s>>>((const float*)F, (const float*)v, n, partials);
+    if (hipGetLastError() != hipSuccess) return LQ_EHIP;
+    k_init_control<<<1, 256, 0, s>>>(partials, g, st);
     return hip_status(hipGetLastError());
 }
 

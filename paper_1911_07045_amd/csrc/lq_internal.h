@@ -190,7 +190,7 @@ struct FireDev {
     double P, nF2, nv2, maxF;
     double dt_max, alpha0, f_inc, f_dec, f_alpha, tol;
     int64_t n_min, max_steps;
-    uint32_t ticket;
+    uint32_t pad;
     int32_t method;   // LQ_METHOD_FIRE / LQ_METHOD_GD / LQ_METHOD_NESTEROV
     double mu;        // Nesterov momentum
 };
@@ -242,10 +242,11 @@ int launch_finalize(const LatDev& L, int prec, bool with_v, const void* bufs, Fi
 int launch_lookahead(const LatDev& L, int prec, const void* q, const void* m, double mu, void* y,
                      void* stream);
 int launch_fill_zero(void* p, int64_t bytes, void* stream);
+// counts: scratch; total: the number of defects, may be NULL (host memory allowed).
 int launch_directors(const LatDev& L, int prec, const void* q, void* dirs, void* lmax, uint8_t* defect,
-                     double thr, unsigned long long* count, void* stream);
-int launch_energy(const LatDev& L, bool l23, int prec, const void* q, double* partials,
-                  EnergyOut* out, uint32_t* ticket, void* stream);
+                     double thr, uint32_t* counts, unsigned long long* total, void* stream);
+// partials: scratch; out: host memory allowed.
+int launch_energy(const LatDev& L, bool l23, int prec, const void* q, double* partials, EnergyOut* out, void* stream);
 int launch_uniaxial(const LatDev& L, int prec, const double* dirs, double S, void* q,
                     void* stream);
 // The members of mem are ordered by kind of step kernel; group[kind] holds
@@ -264,6 +265,7 @@ void launch_brick_batch(bool l23, int prec, const MemberDev* mem, const int* off
                         void* stream);
 int64_t n_step_blocks(const LatDev& L);
 int step_blocks_per_cu(int prec, bool l23, bool l4, int wide, bool two);
-int64_t n_energy_blocks(const LatDev& L);
+int64_t n_energy_blocks(const LatDev& L);  // of the minimizers' initial reduction
+int64_t n_observe_bytes(const LatDev& L);  // scratch of the energy and director kernels
 
 }  // namespace lq
