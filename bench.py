@@ -621,7 +621,7 @@ def traffic_file(workload_name, dtype):
 
 
 TRAFFIC_FILE = traffic_file("multi_colloid256", "f32")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1911_07045_amd", "csrc", f) for f in ("kernels.hip", "lq_site.h", "lq_internal.h")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1911_07045_amd", "csrc", f) for f in ("march.h", "lq_site.h", "lq_internal.h")]
 
 
 def kernel_source_hash():

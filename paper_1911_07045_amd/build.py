@@ -18,6 +18,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", INC, "-I", CSRC] + os.environ.get(
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-ffp-contract=on"]
 SOURCES = [
+    ("march_f64.hip", DEVICE),
+    ("march_f32.hip", DEVICE),
     ("kernels.hip", DEVICE),
     ("brick.hip", DEVICE),
     ("observe.hip", DEVICE),
@@ -39,7 +41,7 @@ def _compile(src, extra):
 
 def build() -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=7) as ex:
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(lambda s: _compile(*s), SOURCES))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs

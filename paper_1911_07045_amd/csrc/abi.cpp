@@ -481,13 +481,13 @@ static void brick_size(bool l23, int64_t S[3]) {
 // that lies in the box (at least 0.6), within the cache's 1.0 M sites in FP64 and
 // 1.9 M in FP32 (134x96x94 FP64: 99 and 111).  Where they were drawn, march against
 // brick: FP64 L1 128x128x60 59.5 and 62.7 (64x128x64 36.3 and 32.2), L2/L3
-// 128x64x80 50.5 and 54.6 (128x64x64 45.0 and 43.7), L4 64x128x64 51.3 and 53.2
+// 101x90x67 58.4 and 61.7 (64x100x64 40.5 and 35.1), L4 64x128x64 51.3 and 53.2
 // (64x80x64 40.1 and 34.4); FP32 L1 112^3 57.0 and 48.0, L2/L3 128x50x60 23.4
 // and 24.4 (64x80x64 22.5 and 19.3).  Boxes that leave more than half of their
 // bricks' sites empty march, unless all of their bricks run at once.
 static bool bricks_for(const lq_params& p, bool l23) {
     const double N = (double)p.n[0] * (double)p.n[1] * (double)p.n[2];
-    const double most = p.prec == LQ_F64 ? (p.L4 != 0.0 ? 4.0e5 : l23 ? 5.3e5 : 9.0e5) : (l23 ? 3.4e5 : 1.25e6);
+    const double most = p.prec == LQ_F64 ? (p.L4 != 0.0 ? 4.0e5 : l23 ? 4.4e5 : 9.0e5) : (l23 ? 3.4e5 : 1.25e6);
     int64_t S[3], nb = 1;
     brick_size(l23, S);
     for (int k = 0; k < 3; ++k) nb *= (p.n[k] + S[k] - 1) / S[k];

@@ -50,14 +50,6 @@ struct BrickStencil {
 // since the error a (magic - 2^32 / d) / 2^32 < 2^-16 stays below 1 / d.
 __device__ __forceinline__ int fast_div(int a, uint64_t magic) { return (int)(((uint64_t)(uint32_t)a * magic) >> 32); }
 
-// Coordinate of a padded position (g = -1 .. n): wrapped, or -1 off an open
-// edge.  Positions past n belong to no site's neighbourhood.
-__device__ __forceinline__ int wrap1(int g, int n, int per) {
-    g = g < 0 ? (per ? n - 1 : -1) : g;
-    g = g == n ? (per ? 0 : -1) : g;
-    return g > n ? -1 : g;
-}
-
 // Padded position of halo site h: the six faces (one-constant kernels, whose
 // stencil has no diagonal), or the whole shell of the padded brick.
 template <bool L23>

@@ -257,6 +257,15 @@ struct BatchGroup {
 };
 int launch_batch_steps(int prec, bool l23, const MemberDev* mem, const BatchGroup group[N_KINDS],
                        const int* fin_off, int total_fin, FireDev* gather, int64_t n_steps, void* stream);
+// Marching kernels (march.h), per element type; mode: MODE_*.
+void launch_march_f64(const LatDev& L, bool l23, int mode, const void* bufs, const void* q, void* F, double* partials,
+                      FireDev* st, int k, void* stream);
+void launch_march_f32(const LatDev& L, bool l23, int mode, const void* bufs, const void* q, void* F, double* partials,
+                      FireDev* st, int k, void* stream);
+void launch_march_batch_f64(bool l23, const MemberDev* mem, const BatchGroup& g, int wide, int k, void* stream);
+void launch_march_batch_f32(bool l23, const MemberDev* mem, const BatchGroup& g, int wide, int k, void* stream);
+int march_blocks_per_cu_f64(bool l23, bool l4, int wide, bool two);
+int march_blocks_per_cu_f32(bool l23, bool l4, int wide);
 // Brick kernels (brick.hip).
 void launch_brick_forces(const LatDev& L, bool l23, int prec, const void* q, void* F, void* stream);
 void launch_brick_step(const LatDev& L, bool l23, int prec, int method, const void* bufs, double* partials,

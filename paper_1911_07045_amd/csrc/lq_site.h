@@ -44,10 +44,20 @@ __device__ __forceinline__ void bst_p(__amdgpu_buffer_rsrc_t r, uint32_t voff, u
 // faster for the one-constant and the FP64 kernels (5% on the 256^3 boxes).
 // The FP32 L2/L3 kernels measured faster with the default policy at every
 // size (14% on the 128^3 bulk box, whose two state buffers fit in the
-// 256 MiB Infinity Cache, 2-4% on the 512^3 patterned wall).  A compile-time
-// choice: a run-time one put a branch in the march loop that cost 1.5%.
-template <typename T, bool L23>
-constexpr int store_policy() { return (L23 && sizeof(T) == 4) ? 0 : 2; }
+// 256 MiB Infinity Cache, 2-4% on the 512^3 patterned wall).  Rows that are no
+// whole number of half lines (ROWS: they are) end tiles inside a line; the L2
+// merges the two tiles' parts under the default policy, while non-temporal
+// parts leave it one by one (FP32 200^3 270 -> 233 us per step, 230x187x141
+// 243 -> 198, FP64 230x187x141 420 -> 388; rows of 64 bytes' multiples are
+// faster non-temporal, FP64 200^3 505 and 520).  That holds for the step
+// kernels of one constant and of FP64 with L4 (101x90x67 71.9 -> 63.7); the
+// force alone (FP64 230x187x141 101 and 139 us) and the FP64 L2/L3 kernels
+// (150^3 256 and 264) stay non-temporal.  A compile-time choice: a
+// run-time one put a branch in the march loop that cost 1.5%.
+template <typename T, bool L23, bool ROWS>
+constexpr int store_policy() { return (L23 && sizeof(T) == 4) || !ROWS ? 0 : 2; }
+template <typename T>
+inline bool whole_rows(int nx) { return ((size_t)nx * sizeof(T)) % 64 == 0; }
 
 // Barrier for data exchanged through LDS only: waits for this wave's LDS
 // operations, not for its global loads and stores (which __syncthreads()
@@ -61,6 +71,15 @@ __device__ __forceinline__ int wrapc(int g, int n, int per) {
     if (!per) return -1;
     g %= n;
     return g < 0 ? g + n : g;
+}
+
+// Coordinate of a padded position g >= -1 of a tile or brick: wrapped, or -1 off
+// an open edge.  Positions past n, where the tile hangs over the box, belong to
+// no site's neighbourhood: -1, so that they load nothing.
+__device__ __forceinline__ int wrap1(int g, int n, int per) {
+    g = g < 0 ? (per ? n - 1 : -1) : g;
+    g = g == n ? (per ? 0 : -1) : g;
+    return g > n ? -1 : g;
 }
 
 __device__ __forceinline__ bool has_nb(uint32_t m, int k, int s) {
