@@ -5,16 +5,15 @@
 // (kernels.hip) waits for memory once per plane; here a block owns one
 // X x Y x Z brick with one thread per site, loads the brick and its one-site
 // halo at once (each thread its own site and IPT halo sites), drifts them into
-// LDS and evaluates the force after a single barrier.  The controller's reads
-// (the stop word, the state and the partial sums of the step before) are
-// issued first and the fields' loads right behind them, so the controller runs
-// while the fields arrive; which of the two buffers holds the state follows
-// from the parity of the step within the call.
+// LDS and evaluates the force after a single barrier.  The controller of the
+// step before runs beside those loads; which of the two buffers holds the state
+// follows from the parity of the step within the call.
 //
 // What bounds a step: up to about 32^3 sites one block's chain (launch, loads,
 // controller, drift, force, reduction); then the loads, which the Infinity
 // Cache serves.  One MI355X, us per FIRE step, marching kernels and bricks:
-//   one-constant FP64  32^3 bulk 15.9 and 8.6, with a colloid 20.0 and 9.2;
+//   one-constant FP64  32^3 bulk 15.9 and 7.6, with a colloid 20.0 and 8.3
+//                      (8.9 and 9.6 with the controller behind the loads);
 //                      64^3 29.6 and 17.1; 96^3 59.7 and 53.3
 //   one-constant FP32  32^3 16.7 and 7.4; 64^3 21.5 and 12.4; 96^3 40.7 and 31.4
 //   L2/L3 FP64         32^3 17.8 and 8.0, with a colloid 51.9 and 16.9
@@ -27,6 +26,12 @@
 #include "lq_site.h"
 
 namespace lq {
+
+// Lattices of at most this many bricks run the controller in one wave: us per
+// step, behind the loads and in one wave, one-constant FP64 32^3 (64 bricks)
+// 8.9 and 7.6, 44^3 (198) 10.7 and 9.7, 64^3 (512) 17.4 and 17.5, 80^3 (1000)
+// 31.5 and 36.0.
+constexpr int WAVE_SUMS = 256;
 
 // The neighbourhood of one site in the brick's padded LDS copy.
 template <typename T, bool L23, bool BULK>
@@ -111,15 +116,36 @@ __device__ __forceinline__ void brick_block(const LatDev& L, const Bufs<T>& b, c
     static_assert(offsetof(DcCtl, halt) == 0 && sizeof(FireDev) % 8 == 0 && CTL_WORDS < 64 && CTL_WORDS < NT, "one word per lane");
     const int tid = threadIdx.x;
 
-    // the controller's reads: the state word by word (lane CTL_WORDS: the stop word)
+    // The controller's reads: the state word by word (lane CTL_WORDS: the stop
+    // word) and the partial sums of step k - 1.  Few of them (WAVE_SUMS) the
+    // first wave sums and runs the controller on while the other waves issue
+    // their loads; many are summed by the whole block, behind those loads.
+    const bool wave_ctl = nblocks <= WAVE_SUMS;
+    const double* part = partials + 4 * (int64_t)((k - 1) & 1) * nblocks;
     uint32_t word = 0;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    const double* part = partials + 4 * (int64_t)((k - 1) & 1) * nblocks;
+    auto add = [&](int i) {
+        const double* p = part + 4 * (int64_t)i;
+        s[0] += p[0]; s[1] += p[1]; s[2] += p[2]; s[3] = fmax(s[3], p[3]);
+    };
+    auto control = [&]() {  // one thread
+        if (k >= 2 && !ctl.halt && !ctl.st.done) fire_control(&ctl.st, s[0], s[1], s[2], s[3]);
+    };
     if (STEP) {
-        // one load for all of them: st[slot] then the stop word behind st[1]
+        // one load for all words: st[slot] then the stop word behind st[1]
         if (tid <= CTL_WORDS)
             word = ((const uint32_t*)st)[tid < CTL_WORDS ? (k >= 2 ? (k & 1) : 0) * CTL_WORDS + tid : 2 * CTL_WORDS];
-        if (k >= 2 && tid < nblocks) {
+        if (wave_ctl) {
+            if (tid < 64) {
+                if (k >= 2) {
+                    for (int i = tid; i < nblocks; i += 64) add(i);
+                    s[0] = wave_sum(s[0]); s[1] = wave_sum(s[1]); s[2] = wave_sum(s[2]); s[3] = wave_max(s[3]);
+                }
+                if (tid <= CTL_WORDS) ((uint32_t*)&ctl)[tid] = word;
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if (tid == 63) control();
+            }
+        } else if (k >= 2 && tid < nblocks) {
             const double* p = part + 4 * (int64_t)tid;
             s[0] = p[0]; s[1] = p[1]; s[2] = p[2]; s[3] = p[3];
         }
@@ -183,15 +209,15 @@ __device__ __forceinline__ void brick_block(const LatDev& L, const Bufs<T>& b, c
 
     T cv = T(1), cF = T(0), dt = T(0), hdt = T(0);
     if (STEP) {
-        // the controller of step k - 1 (dc_begin's sums, in its order)
-        if (tid <= CTL_WORDS) ((uint32_t*)&ctl)[tid] = word;
-        if (k >= 2) {
-            for (int i = tid + NT; i < nblocks; i += NT) {
-                const double* p = part + 4 * (int64_t)i;
-                s[0] += p[0]; s[1] += p[1]; s[2] += p[2]; s[3] = fmax(s[3], p[3]);
+        if (!wave_ctl) {
+            if (tid <= CTL_WORDS) ((uint32_t*)&ctl)[tid] = word;
+            if (k >= 2) {
+                for (int i = tid + NT; i < nblocks; i += NT) add(i);
+                block_reduce4<true, true>(s, scratch);
+            } else {
+                lds_barrier();
             }
-            block_reduce4<true, true>(s, scratch);
-            if (tid == 0 && !ctl.halt && !ctl.st.done) fire_control(&ctl.st, s[0], s[1], s[2], s[3]);
+            if (tid == 0) control();
         }
         lds_barrier();
         const int halt = ctl.halt, stop = halt || ctl.st.done;
@@ -305,6 +331,22 @@ __global__ __launch_bounds__(Brick<L23>::N) __attribute__((amdgpu_waves_per_eu(!
     brick_block<T, L23, L23, MODE_FIRE>(M.L, b, nullptr, nullptr, M.partials, M.st, M.nblocks, blk - off[m], k);
 }
 
+// The controller on a call's last step (dc_final), with the step kernels' sums.
+template <int NT>
+__device__ __forceinline__ void brick_final(FireDev* st, const double* partials, int nblocks, int k_steps) {
+    __shared__ double scratch[NT / 64][4];
+    dc_final<NT>(st, partials, nblocks, k_steps, scratch, nblocks <= WAVE_SUMS ? 64 : NT);
+}
+template <int NT>
+__global__ __launch_bounds__(NT) void k_brick_control(FireDev* st, const double* partials, int nblocks, int k_steps) {
+    brick_final<NT>(st, partials, nblocks, k_steps);
+}
+template <int NT>
+__global__ __launch_bounds__(NT) void k_brick_batch_control(const MemberDev* __restrict__ mem, int k_steps) {
+    const MemberDev& M = mem[blockIdx.x];
+    brick_final<NT>(M.st, M.partials, M.nblocks, k_steps);
+}
+
 // ---------------------------------------------------------------------------
 // launchers
 template <typename T, int MODE>
@@ -340,6 +382,19 @@ void launch_brick_step(const LatDev& L, bool l23, int prec, int method, const vo
     if (method == LQ_METHOD_GD) launch_brick_mode<MODE_GD>(L, l23, prec, bufs, partials, st, k, s);
     else if (method == LQ_METHOD_NESTEROV) launch_brick_mode<MODE_NAG>(L, l23, prec, bufs, partials, st, k, s);
     else launch_brick_mode<MODE_FIRE>(L, l23, prec, bufs, partials, st, k, s);
+}
+
+void launch_brick_control(bool l23, FireDev* st, const double* partials, int nblocks, int k_steps, void* stream) {
+    hipStream_t s = (hipStream_t)stream;
+    if (l23) k_brick_control<Brick<true>::N><<<1, Brick<true>::N, 0, s>>>(st, partials, nblocks, k_steps);
+    else k_brick_control<Brick<false>::N><<<1, Brick<false>::N, 0, s>>>(st, partials, nblocks, k_steps);
+}
+
+void launch_brick_batch_control(bool l23, const MemberDev* mem, int n, int k_steps, void* stream) {
+    if (n <= 0) return;
+    hipStream_t s = (hipStream_t)stream;
+    if (l23) k_brick_batch_control<Brick<true>::N><<<n, Brick<true>::N, 0, s>>>(mem, k_steps);
+    else k_brick_batch_control<Brick<false>::N><<<n, Brick<false>::N, 0, s>>>(mem, k_steps);
 }
 
 void launch_brick_batch(bool l23, int prec, const MemberDev* mem, const int* off, int n, int bricks, int k,

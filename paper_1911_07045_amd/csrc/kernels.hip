@@ -8,30 +8,6 @@
 
 namespace lq {
 
-// After the k_steps step kernels of a call: the controller on the last
-// step's reduction (the same sums, in the same order, as in a step kernel
-// of NT threads), or the state the run stopped with, into st[0].
-template <int NT>
-__device__ void dc_final(FireDev* st, const double* partials, int nblocks, int k_steps, double (*scratch)[4]) {
-    DcCtl* ctl = (DcCtl*)(st + 2);
-    if (ctl->halt) {
-        if (threadIdx.x == 0) {
-            const int sl = ctl->slot;
-            if (sl != 0) st[0] = st[sl];
-            ctl->halt = 0;
-        }
-        return;
-    }
-    if (k_steps <= 0) return;
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    sum_partials(partials + 4 * (int64_t)(k_steps & 1) * nblocks, nblocks, s, scratch);
-    if (threadIdx.x == 0) {
-        FireDev c = st[k_steps >= 2 ? ((k_steps - 1) & 1) : 0];
-        fire_control(&c, s[0], s[1], s[2], s[3]);
-        st[0] = c;
-    }
-}
-
 template <int NT>
 __global__ __launch_bounds__(NT) void k_dc_control(FireDev* st, const double* partials, int nblocks, int k_steps) {
     __shared__ double scratch[NT / 64][4];
@@ -120,7 +96,7 @@ __global__ __launch_bounds__(256) void k_init_reduce(const T* __restrict__ F, co
 __global__ __launch_bounds__(256) void k_init_control(const double* partials, int nblocks, FireDev* st) {
     __shared__ double scratch[4][4];
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    sum_partials(partials, nblocks, s, scratch);
+    sum_partials(partials, nblocks, s, scratch, 256);
     if (threadIdx.x == 0) {
         FireDev c = *st;
         fire_control(&c, s[0], s[1], s[2], s[3]);
@@ -246,7 +222,11 @@ int launch_fire_steps(const LatDev& L, bool l23, int prec, int method, const voi
         if (e != hipSuccess) return LQ_EHIP;
     }
     // the controller on the last step's reduction, with the step kernel's block size
-    const int nt = step_threads(prec, l23, L.kind), nb = (int)n_step_blocks(L), kl = step_index(n_steps);
+    if (L.kind == KIND_BRICK) {
+        launch_brick_control(l23, st, partials, (int)n_step_blocks(L), step_index(n_steps), stream);
+        return hip_status(hipGetLastError());
+    }
+    const int nt = tile_threads(prec, l23, L.kind), nb = (int)n_step_blocks(L), kl = step_index(n_steps);
     if (nt == 1024) k_dc_control<1024><<<1, 1024, 0, s>>>(st, partials, nb, kl);
     else if (nt == 512) k_dc_control<512><<<1, 512, 0, s>>>(st, partials, nb, kl);
     else if (nt == 256) k_dc_control<256><<<1, 256, 0, s>>>(st, partials, nb, kl);
@@ -327,8 +307,9 @@ int launch_batch_steps(int prec, bool l23, const MemberDev* mem, const BatchGrou
                            group[KIND_BRICK].blocks, k, stream);
         if (hipGetLastError() != hipSuccess) return LQ_EHIP;
     }
-    for (int g = 0; g < N_KINDS; ++g)
-        launch_batch_control(step_threads(prec, l23, g), gm[g], group[g].n, step_index(n_steps), s);
+    for (int w = KIND_NARROW; w <= KIND_WIDE; ++w)
+        launch_batch_control(tile_threads(prec, l23, w), gm[w], group[w].n, step_index(n_steps), s);
+    launch_brick_batch_control(l23, gm[KIND_BRICK], group[KIND_BRICK].n, step_index(n_steps), stream);
     if (hipGetLastError() != hipSuccess) return LQ_EHIP;
     if (prec == LQ_F64) k_batch_finalize<double><<<total_fin, 256, 0, s>>>(mem, fin_off, n_members);
     else k_batch_finalize<float><<<total_fin, 256, 0, s>>>(mem, fin_off, n_members);

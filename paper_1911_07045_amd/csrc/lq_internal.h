@@ -133,12 +133,8 @@ inline int tile_y_w(int prec, bool l23) {
 inline int tile_x(int prec, bool l23, int wide) { return wide ? tile_x_w<1>(prec, l23) : tile_x_w<0>(prec, l23); }
 inline int tile_y(int prec, bool l23, int wide) { return wide ? tile_y_w<1>(prec, l23) : tile_y_w<0>(prec, l23); }
 inline int tile_threads(int prec, bool l23, int wide) { return tile_x(prec, l23, wide) * tile_y(prec, l23, wide); }
-inline int brick_threads(bool l23) { return l23 ? Brick<true>::N : Brick<false>::N; }
 // kinds of step kernel: marching tiles (narrow, wide) and bricks
 enum : int { KIND_NARROW = 0, KIND_WIDE = 1, KIND_BRICK = 2, N_KINDS = 3 };
-inline int step_threads(int prec, bool l23, int kind) {
-    return kind == KIND_BRICK ? brick_threads(l23) : tile_threads(prec, l23, kind);
-}
 // a lattice narrower than one wide tile takes the narrow one
 inline int tile_wide_for(int64_t nx, int prec, bool l23) { return nx >= tile_x_w<1>(prec, l23) ? 1 : 0; }
 
@@ -270,6 +266,8 @@ int march_blocks_per_cu_f32(bool l23, bool l4, int wide);
 void launch_brick_forces(const LatDev& L, bool l23, int prec, const void* q, void* F, void* stream);
 void launch_brick_step(const LatDev& L, bool l23, int prec, int method, const void* bufs, double* partials,
                        FireDev* st, int k, void* stream);
+void launch_brick_control(bool l23, FireDev* st, const double* partials, int nblocks, int k_steps, void* stream);
+void launch_brick_batch_control(bool l23, const MemberDev* mem, int n, int k_steps, void* stream);
 void launch_brick_batch(bool l23, int prec, const MemberDev* mem, const int* off, int n, int bricks, int k,
                         void* stream);
 int64_t n_step_blocks(const LatDev& L);

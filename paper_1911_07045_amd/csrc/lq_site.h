@@ -645,10 +645,10 @@ __device__ inline void fire_control(FireDev* st, double P, double nF2, double nv
 
 // Sums the partials of nblocks blocks in block order (every block of a
 // kernel that calls this gets the same sums: they depend on the block size
-// and nblocks only).
+// and nblocks only); the first `stride` threads read.
 __device__ __forceinline__ void sum_partials(const double* partials, int nblocks, double s[4],
-                                             double (*scratch)[4]) {
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
+                                             double (*scratch)[4], int stride) {
+    for (int b = (int)threadIdx.x < stride ? (int)threadIdx.x : nblocks; b < nblocks; b += stride) {
         const double* p = partials + 4 * (int64_t)b;
         s[0] += p[0]; s[1] += p[1]; s[2] += p[2]; s[3] = fmax(s[3], p[3]);
     }
@@ -656,6 +656,31 @@ __device__ __forceinline__ void sum_partials(const double* partials, int nblocks
     block_reduce4(s, scratch);
 }
 
+
+// After the k_steps step kernels of a call: the controller on the last
+// step's reduction (the same sums, in the same order, as in a step kernel
+// of NT threads; its first `stride` threads sum), or the state the run stopped with, into st[0].
+template <int NT>
+__device__ __forceinline__ void dc_final(FireDev* st, const double* partials, int nblocks, int k_steps,
+                                         double (*scratch)[4], int stride = NT) {
+    DcCtl* ctl = (DcCtl*)(st + 2);
+    if (ctl->halt) {
+        if (threadIdx.x == 0) {
+            const int sl = ctl->slot;
+            if (sl != 0) st[0] = st[sl];
+            ctl->halt = 0;
+        }
+        return;
+    }
+    if (k_steps <= 0) return;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    sum_partials(partials + 4 * (int64_t)(k_steps & 1) * nblocks, nblocks, s, scratch, stride);
+    if (threadIdx.x == 0) {
+        FireDev c = st[k_steps >= 2 ? ((k_steps - 1) & 1) : 0];
+        fire_control(&c, s[0], s[1], s[2], s[3]);
+        st[0] = c;
+    }
+}
 
 // Blocks are dispatched round-robin over the 8 XCDs: XCD x runs the blocks
 // x, x + 8, ...  They take the x-th contiguous share of the work (the first

@@ -412,7 +412,7 @@ __device__ bool dc_begin(FireDev* st, const double* partials, int nblocks, int k
     __syncthreads();
     if (ci[2]) return true;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    if (k >= 2) sum_partials(partials + 4 * (int64_t)((k - 1) & 1) * nblocks, nblocks, s, scratch);
+    if (k >= 2) sum_partials(partials + 4 * (int64_t)((k - 1) & 1) * nblocks, nblocks, s, scratch, blockDim.x);
     if (threadIdx.x == 0) {
         FireDev c = st[k >= 2 ? (k & 1) : 0];
         if (k >= 2 && !c.done) fire_control(&c, s[0], s[1], s[2], s[3]);
