@@ -87,7 +87,14 @@ struct Stencil {
 // spread over all threads one (site, component) pair at a time), then drifted
 // (steering, first half kick, q += dt v) into an LDS slot.  Loads run one
 // plane ahead of the drift, so the loads of plane i+1 are in flight while the
-// force of plane i-1 is evaluated.
+// force of plane i-1 is evaluated.  Steps march upwards and downwards in turn
+// (`down`, by the parity of the step count): the planes that one step wrote
+// last are the first that the next one reads, while the Infinity Cache still
+// holds them.  That pays where the state is stored with the default policy (us
+// per step, FP32 L2/L3 201x163x95 slab 145.7 -> 134.3, 256^3 437 -> 426;
+// one-constant 230x187x141 FP32 198 -> 181, FP64 371 -> 361) and is neutral
+// with the non-temporal one.  The FP64 L4 kernels march upwards always
+// (201x163x95 with a colloid 358, in turn 363).
 template <typename T, bool L23, int W>
 __device__ __forceinline__ void ring_pos(int r, int& px, int& py) {
     constexpr int PX = Tile<T, L23, W>::PX, PY = Tile<T, L23, W>::PY;
@@ -122,7 +129,7 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
                                       const T* __restrict__ v_in, const T* __restrict__ F_in,
                                       T* __restrict__ q_out, T* __restrict__ v_out,
                                       T* __restrict__ F_out, T cv, T cF, T dt, T hdt, int x0, int y0,
-                                      int z0, int zc, T (*sq)[5][Tile<T, L23, W>::PY][Tile<T, L23, W>::PX],
+                                      int z0, int zc, bool down, T (*sq)[5][Tile<T, L23, W>::PY][Tile<T, L23, W>::PX],
                                       uint8_t (*sm)[Tile<T, L23, W>::PY][Tile<T, L23, W>::PX], double red[4],
                                       const PlaneBits plane_bulk) {
     using G = Tile<T, L23, W>;
@@ -175,11 +182,13 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
     const __amdgpu_buffer_rsrc_t rF_out = field_rsrc(F_out, fb);
     const __amdgpu_buffer_rsrc_t rmask = field_rsrc(L.mask, (uint32_t)N);
     constexpr uint32_t NONE = 0xFFFFFFFFu;  // past every resource: loads give 0, stores drop
+    // global z of plane i of the march (1 .. zc: the chunk's planes)
+    auto z_of = [&](int i) { return down ? z0 + zc - i : z0 - 1 + i; };
     // Branch-free loads: an invalid position gets an offset past the end of the
     // buffer instead of a branch, so the wait counts stay exact and the stores
     // of the previous plane can drain while this plane is drifted.
     auto load = [&](int i, Raw& R) {
-        const int wz = (i >= 0 && i <= zc + 1) ? wrapc(z0 - 1 + i, L.nz, L.per[2]) : -1;
+        const int wz = (i >= 0 && i <= zc + 1) ? wrapc(z_of(i), L.nz, L.per[2]) : -1;
         const bool ok = sxy_own >= 0 && wz >= 0;
         const uint32_t site = (uint32_t)(sxy_own + nxy * wz);
         const uint32_t off = ok ? site * (uint32_t)sizeof(T) : NONE;
@@ -253,6 +262,8 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
         }
     };
     auto slot_of = [](int i) { return (i + NS) & (NS - 1); };
+    // plane of the chunk (1-based from its bottom, as the plane flags count)
+    auto plane_of = [&](int f) { return down ? zc + 1 - f : f; };
 
     // Loads run one plane ahead: iteration j drifts plane j (loaded during
     // iteration j-1), issues the loads of plane j+1, and evaluates and stores
@@ -288,7 +299,7 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
         AnchRow<T> A;
         if (!BULK && W == 1 && !(L23 && sizeof(T) == 8)) {
             const int f = j - 1;
-            const bool bulk_plane = bulk_plane_of(plane_bulk, f);
+            const bool bulk_plane = bulk_plane_of(plane_bulk, plane_of(f));
             // only waves with an anchored site issue the loads
             if (!bulk_plane && __builtin_amdgcn_ballot_w64((m_newer & M_ANCH) != 0) != 0)
                 anch_load(L, (m_newer & M_ANCH) ? a_newer : 0, A);
@@ -300,7 +311,7 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
         drift(R, slot_of(j), q_newer, v1_newer, m_newer);
         if (!BULK) {
             const bool anch = own_xy && j >= 1 && j <= zc && (m_newer & M_ANCH);
-            const uint32_t sj = (uint32_t)(gx + L.nx * gy + nxy * (z0 + j - 1));
+            const uint32_t sj = (uint32_t)(gx + L.nx * gy + nxy * z_of(j));
             a_newer = (int)__builtin_amdgcn_raw_buffer_load_b32(ranch, (int)(anch ? sj * 4u : NONE), 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -314,12 +325,12 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
         {
             const int f = j - 1;  // plane whose force is evaluated
             const bool in_chunk = f >= 1;
-            const int s = gx + L.nx * gy + nxy * (z0 + f - 1);
+            const int s = gx + L.nx * gy + nxy * z_of(f);
             const uint32_t off = (own_xy && in_chunk) ? (uint32_t)s * (uint32_t)sizeof(T) : NONE;
             const bool live = own_xy && in_chunk && (m_older & M_SIM);
             Stencil<T, L23, BULK, W> P;
             P.q = sq; P.m = sm;
-            P.s[0] = slot_of(f - 1); P.s[1] = slot_of(f); P.s[2] = slot_of(f + 1);
+            P.s[0] = slot_of(down ? f + 1 : f - 1); P.s[1] = slot_of(f); P.s[2] = slot_of(down ? f - 1 : f + 1);
             P.cx = tx + 1; P.cy = ty + 1;
             T F[5];
             // a plane whose 3 x 3 x 3 neighbourhoods are all full bulk sites
@@ -333,7 +344,7 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
             if (L23 && !in_chunk) {
 #pragma unroll
                 for (int c = 0; c < 5; ++c) F[c] = T(0);
-            } else if (W == 1 && !BULK && bulk_plane_of(plane_bulk, f)) {
+            } else if (W == 1 && !BULK && bulk_plane_of(plane_bulk, plane_of(f))) {
                 Stencil<T, L23, true, W> PB;
                 PB.q = sq; PB.m = sm;
                 PB.s[0] = P.s[0]; PB.s[1] = P.s[1]; PB.s[2] = P.s[2];
@@ -401,8 +412,8 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
 // in the same order give every block the same result), so that no block
 // waits for a last one to finish the previous kernel.  Block 0 keeps the
 // new state in st[(k - 1) & 1].  Returns true (every thread) when the run has
-// stopped; the step's parameters go to cd (dt, c_v, c_F, mu) and ci (cur,
-// stop; ci[2] takes the stop word).
+// stopped; the step's parameters go to cd (dt, c_v, c_F, mu) and ci (cur with
+// the parity of the step count in bit 1, stop; ci[2] takes the stop word).
 __device__ bool dc_begin(FireDev* st, const double* partials, int nblocks, int k, int bid,
                          double (*scratch)[4], double* cd, int* ci) {
     DcCtl* ctl = (DcCtl*)(st + 2);
@@ -425,7 +436,7 @@ __device__ bool dc_begin(FireDev* st, const double* partials, int nblocks, int k
             }
         }
         cd[0] = c.dt; cd[1] = c.c_v; cd[2] = c.c_F; cd[3] = c.mu;
-        ci[0] = c.cur; ci[1] = stop;
+        ci[0] = c.cur | (int)(c.step & 1) << 1; ci[1] = stop;
     }
     __syncthreads();
     return ci[1] != 0;
@@ -453,9 +464,11 @@ __device__ __forceinline__ void step_block(const LatDev& L, const Bufs<T>& b, co
     const T *q_in, *v_in = nullptr, *F_in = nullptr;
     T *q_out = nullptr, *v_out = nullptr, *F_out;
     T cv = T(1), cF = T(0), dt = T(0), hdt = T(0);
+    bool down = false;
     if (STEP) {
         if (dc_begin(st, partials, nblocks, k, bid, scratch, ctl_d, ctl_i)) return;
-        const int cur = ctl_i[0];
+        const int cur = ctl_i[0] & 1;
+        down = !(L4 && sizeof(T) == 8) && (ctl_i[0] & 2) != 0;
         const double dtd = ctl_d[0], c_v = ctl_d[1], c_F = ctl_d[2], mu = ctl_d[3];
         // selects rather than indexing by cur, which would put b in scratch
         q_in = cur ? b.q[1] : b.q[0]; v_in = cur ? b.v[1] : b.v[0]; F_in = cur ? b.F[1] : b.F[0];
@@ -482,10 +495,10 @@ __device__ __forceinline__ void step_block(const LatDev& L, const Bufs<T>& b, co
 #pragma unroll
             for (int w = 0; w < PLANE_WORDS; ++w) all.w[w] = ~(uint64_t)0;
             march<T, L23, L4, MODE, true, W, ROWS>(L, q_in, v_in, F_in, q_out, v_out, F_out, cv, cF, dt, hdt, x0, y0, z0,
-                                             zc, sq, sm, red, all);
+                                             zc, down, sq, sm, red, all);
         } else {
             march<T, L23, L4, MODE, false, W, ROWS>(L, q_in, v_in, F_in, q_out, v_out, F_out, cv, cF, dt, hdt, x0, y0, z0,
-                                              zc, sq, sm, red, L.tile_planes[i]);
+                                              zc, down, sq, sm, red, L.tile_planes[i]);
         }
     }
     if (STEP) {
@@ -547,39 +560,36 @@ static int blocks_per_cu_t(bool l23, bool l4, int wide) {
     if (l4) return wide ? blocks_per_cu<T, true, true, 1>() : blocks_per_cu<T, true, true, 0>();
     return wide ? blocks_per_cu<T, true, false, 1>() : blocks_per_cu<T, true, false, 0>();
 }
+template <typename T, bool L23, bool L4, int MODE, int W, bool TWO, bool ROWS>
+static void launch_one(const LatDev& L, const Bufs<T>& b, const void* q, void* F, double* partials, FireDev* st, int k,
+                       hipStream_t s) {
+    k_march<T, L23, L4, MODE, W, TWO, ROWS><<<dim3((unsigned)n_step_blocks(L)), Tile<T, L23, W>::N, 0, s>>>(
+        L, b, (const T*)q, (T*)F, partials, st, k);
+}
+
 template <typename T, int MODE, int W>
 static void launch_march(const LatDev& L, bool l23, const Bufs<T>& b, const void* q, void* F, double* partials,
                          FireDev* st, int k, hipStream_t s) {
-    const dim3 g((unsigned)n_step_blocks(L));
-    if constexpr (sizeof(T) == 8 && W == 1) {
-        if (l23 && L.L4 == 0.0 && L.two_waves) {
-            k_march<T, true, false, MODE, W, true><<<g, Tile<T, true, W>::N, 0, s>>>(L, b, (const T*)q, (T*)F,
-                                                                                 partials, st, k);
-            return;
-        }
-    }
-    if constexpr (MODE != MODE_FORCE) {
-        if (!whole_rows<T>(L.nx)) {
-            if (!l23) {
-                k_march<T, false, false, MODE, W, false, false><<<g, Tile<T, false, W>::N, 0, s>>>(L, b, (const T*)q, (T*)F,
-                                                                                               partials, st, k);
+    constexpr bool STEP = MODE != MODE_FORCE, F64 = sizeof(T) == 8;
+    // the store policy (store_policy): the force and the FP32 L2/L3/L4 kernels have one
+    const bool rows = !STEP || (whole_rows<T>(L.nx) && !(F64 && l23 && state_fits_cache<T>(L.N)));
+    if (l23 && L.L4 != 0.0) {
+        if (rows) launch_one<T, true, true, MODE, W, false, true>(L, b, q, F, partials, st, k, s);
+        else launch_one<T, true, true, MODE, W, false, !(F64 && STEP)>(L, b, q, F, partials, st, k, s);
+    } else if (l23) {
+        if constexpr (F64 && W == 1) {
+            if (L.two_waves) {
+                if (rows) launch_one<T, true, false, MODE, W, true, true>(L, b, q, F, partials, st, k, s);
+                else launch_one<T, true, false, MODE, W, true, !(F64 && STEP)>(L, b, q, F, partials, st, k, s);
                 return;
             }
-            if constexpr (sizeof(T) == 8) {
-                if (L.L4 != 0.0) {
-                    k_march<T, true, true, MODE, W, false, false><<<g, Tile<T, true, W>::N, 0, s>>>(
-                        L, b, (const T*)q, (T*)F, partials, st, k);
-                    return;
-                }
-            }
         }
+        if (rows) launch_one<T, true, false, MODE, W, false, true>(L, b, q, F, partials, st, k, s);
+        else launch_one<T, true, false, MODE, W, false, !(F64 && STEP)>(L, b, q, F, partials, st, k, s);
+    } else {
+        if (rows) launch_one<T, false, false, MODE, W, false, true>(L, b, q, F, partials, st, k, s);
+        else launch_one<T, false, false, MODE, W, false, !STEP>(L, b, q, F, partials, st, k, s);
     }
-    if (l23 && L.L4 != 0.0)
-        k_march<T, true, true, MODE, W><<<g, Tile<T, true, W>::N, 0, s>>>(L, b, (const T*)q, (T*)F, partials, st, k);
-    else if (l23)
-        k_march<T, true, false, MODE, W><<<g, Tile<T, true, W>::N, 0, s>>>(L, b, (const T*)q, (T*)F, partials, st, k);
-    else
-        k_march<T, false, false, MODE, W><<<g, Tile<T, false, W>::N, 0, s>>>(L, b, (const T*)q, (T*)F, partials, st, k);
 }
 
 template <typename T, int MODE>
