@@ -472,29 +472,29 @@ static void brick_size(bool l23, int64_t S[3]) {
 // Small lattices step in bricks (brick.hip).  A marching block waits for memory
 // once per plane, a brick once per step, so bricks win while a step is bound by
 // waits rather than by bytes: us per step, march against brick, one-constant
-// FP64 32^3 15.9 and 8.6, 64^3 29.6 and 17.1, 96^3 59.7 and 53.3.  A brick loads
-// its halo again (1.9 sites per site, 2.5 with L2/L3), which the Infinity Cache
-// serves while both state buffers fit in it (2 x 15 values per site, 256 MiB):
-// 112^3 FP64 83.5 and 102, 128^3 FP32 64.6 and 73.0.  The L2/L3/L4 kernels load
-// the whole shell and cross earlier.  Marching tiles that hang over the box's
-// edge cost their full width, so the limits hold for the share of the tiles
-// that lies in the box (at least 0.6), within the cache's 1.0 M sites in FP64 and
-// 1.9 M in FP32 (134x96x94 FP64: 99 and 111).  Where they were drawn, march against
-// brick: FP64 L1 128x128x60 59.5 and 62.7 (64x128x64 36.3 and 32.2), L2/L3
-// 101x90x67 58.4 and 61.7 (64x100x64 40.5 and 35.1), L4 64x128x64 51.3 and 53.2
-// (64x80x64 40.1 and 34.4); FP32 L1 112^3 57.0 and 48.0, L2/L3 128x50x60 23.4
-// and 24.4 (64x80x64 22.5 and 19.3).  Boxes that leave more than half of their
-// bricks' sites empty march, unless all of their bricks run at once.
+// FP64 32^3 15.9 and 7.6, 64^3 29.1 and 17.8.  A brick loads its halo again (1.9
+// sites per site, 2.5 with L2/L3), which costs more than the waits once the
+// march streams from the Infinity Cache: 101x90x67 FP64 37.8 and 44.2, 104^3 FP32
+// 37.5 and 44.4.  Marching tiles that hang over the box's edge cost their full
+// width, so the limits hold for the share of the tiles that lies in the box (at
+// least 0.6).  Where they were drawn, march against brick (in bulk, and with a
+// colloid, whose boundary planes lengthen a march and leave bricks alone):
+// FP64 L1 61x70x90 28.5 and 29.7, 33.6 and 30.2; 90x90x70 37.3 and 42.6, 43.3 and
+// 42.9; FP32 L1 96^3 31.8 and 32.2, 37.0 and 33.2; 104^3 with one 43.4 and 45.6;
+// FP64 L2/L3 64x100x64 32.7 and 35.4, 63.5 and 44.4; L4 64x80x64 37.9 and 35.1;
+// FP32 L2/L3 128x50x60 23.4 and 24.4, 64x80x64 21.1 and 19.4.  Boxes that leave
+// more than half of their bricks' sites empty march, unless all of their bricks
+// run at once.
 static bool bricks_for(const lq_params& p, bool l23) {
     const double N = (double)p.n[0] * (double)p.n[1] * (double)p.n[2];
-    const double most = p.prec == LQ_F64 ? (p.L4 != 0.0 ? 4.0e5 : l23 ? 4.4e5 : 9.0e5) : (l23 ? 3.4e5 : 1.25e6);
+    const double most = p.prec == LQ_F64 ? (p.L4 != 0.0 ? 4.0e5 : l23 ? 4.4e5 : 3.7e5) : (l23 ? 3.4e5 : 7.0e5);
     int64_t S[3], nb = 1;
     brick_size(l23, S);
     for (int k = 0; k < 3; ++k) nb *= (p.n[k] + S[k] - 1) / S[k];
     const int wide = tile_wide_for(p.n[0], p.prec, l23);
     const int64_t TX = tile_x(p.prec, l23, wide), TY = tile_y(p.prec, l23, wide);
     const double marched = (double)((p.n[0] + TX - 1) / TX * TX) * (double)((p.n[1] + TY - 1) / TY * TY) * (double)p.n[2];
-    return N <= (p.prec == LQ_F64 ? 1.0e6 : 1.9e6) && N * std::max(0.6, N / marched) <= most && (nb <= 256 || 2.0 * N >= (double)(nb * S[0] * S[1] * S[2]));
+    return N * std::max(0.6, N / marched) <= most && (nb <= 256 || 2.0 * N >= (double)(nb * S[0] * S[1] * S[2]));
 }
 
 // The bricks of a lattice, x fastest: bit z of a brick's byte is set when the

@@ -14,8 +14,8 @@
 // Cache serves.  One MI355X, us per FIRE step, marching kernels and bricks:
 //   one-constant FP64  32^3 bulk 15.9 and 7.6, with a colloid 20.0 and 8.3
 //                      (8.9 and 9.6 with the controller behind the loads);
-//                      64^3 29.6 and 17.1; 96^3 59.7 and 53.3
-//   one-constant FP32  32^3 16.7 and 7.4; 64^3 21.5 and 12.4; 96^3 40.7 and 31.4
+//                      64^3 29.6 and 17.1
+//   one-constant FP32  32^3 16.7 and 7.4; 64^3 21.5 and 12.4; 75x81x93 32.1 and 27.2
 //   L2/L3 FP64         32^3 17.8 and 8.0, with a colloid 51.9 and 16.9
 // and 20 FP32 boxes of 16 to 64 sites a side in one batch 61 and 36.  Brick
 // shapes for 44^3 and 64^3 FP32 one-constant: 8x4x4 11.5 and 22.7, 8x8x4 9.6 and

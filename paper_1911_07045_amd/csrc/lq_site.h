@@ -49,11 +49,13 @@ __device__ __forceinline__ void bst_p(__amdgpu_buffer_rsrc_t r, uint32_t voff, u
 // merges the two tiles' parts under the default policy, while non-temporal
 // parts leave it one by one (FP32 200^3 270 -> 233 us per step, 230x187x141
 // 243 -> 198, FP64 230x187x141 420 -> 388; rows of 64 bytes' multiples are
-// faster non-temporal, FP64 200^3 505 and 520).  The FP64 L2/L3/L4 step kernels
-// take the default policy there and where both state buffers fit in the
-// Infinity Cache (L2/L3 101x90x67 57.4 -> 44.0, 96^3 69.3 -> 56.3, 201x163x95
-// 240 -> 228; 128^3 122.6 and 128.2; L4 96^3 102 -> 91).  The force alone stays non-temporal (FP64
-// 230x187x141 101 and 139 us).  A compile-time choice: a
+// faster non-temporal, FP64 200^3 505 and 520).  Where both state buffers fit
+// in the Infinity Cache the step kernels take the default policy too: the
+// next step then reads what this one wrote from there (FP32 128^3 66.1 -> 52.5,
+// 112^3 57.1 -> 40.4; FP64 128x128x60 57.7 -> 48.9; FP64 L2/L3 96^3 69.3 -> 56.3,
+// L4 96^3 102 -> 91; beyond it FP64 L2/L3 128^3 122.6 and 128.2, 256^3 FP32 414 and
+// 420).  FP64 L2/L3 with ragged rows: 201x163x95 240 -> 228.  The force alone
+// stays non-temporal (FP64 230x187x141 101 and 139 us).  A compile-time choice: a
 // run-time one put a branch in the march loop that cost 1.5%.
 template <typename T, bool L23, bool ROWS>
 constexpr int store_policy() { return (L23 && sizeof(T) == 4) || !ROWS ? 0 : 2; }

@@ -572,7 +572,7 @@ static void launch_march(const LatDev& L, bool l23, const Bufs<T>& b, const void
                          FireDev* st, int k, hipStream_t s) {
     constexpr bool STEP = MODE != MODE_FORCE, F64 = sizeof(T) == 8;
     // the store policy (store_policy): the force and the FP32 L2/L3/L4 kernels have one
-    const bool rows = !STEP || (whole_rows<T>(L.nx) && !(F64 && l23 && state_fits_cache<T>(L.N)));
+    const bool rows = !STEP || (whole_rows<T>(L.nx) && !state_fits_cache<T>(L.N));
     if (l23 && L.L4 != 0.0) {
         if (rows) launch_one<T, true, true, MODE, W, false, true>(L, b, q, F, partials, st, k, s);
         else launch_one<T, true, true, MODE, W, false, !(F64 && STEP)>(L, b, q, F, partials, st, k, s);

@@ -103,10 +103,10 @@ def test_bricks(ora, shape, periodic, elastic):
 
 
 # just above the sizes that bricks serve: narrow tiles, then wide ones
-# (rows of whole half lines and ragged ones)
-MARCH64 = [("one", (61, 142, 120)), ("one", (129, 150, 81)), ("one", (136, 150, 81)), ("l23", (61, 100, 100)), ("l23", (65, 120, 120)),
+# (rows of whole half lines, with the state in the cache or beyond it, and ragged ones)
+MARCH64 = [("one", (61, 142, 120)), ("one", (64, 100, 80)), ("one", (129, 150, 81)), ("one", (136, 150, 81)), ("l23", (61, 100, 100)), ("l23", (65, 120, 120)),
            ("chiral", (61, 100, 80)), ("chiral", (65, 100, 105))]
-MARCH32 = [("one", (100, 142, 120)), ("one", (129, 140, 120)), ("one", (144, 140, 120)), ("l23", (61, 80, 81)), ("l23", (65, 95, 93)),
+MARCH32 = [("one", (100, 142, 120)), ("one", (128, 96, 90)), ("one", (129, 140, 120)), ("one", (144, 140, 120)), ("l23", (61, 80, 81)), ("l23", (65, 95, 93)),
            ("chiral", (61, 80, 81)), ("chiral", (65, 95, 93))]
 
 
