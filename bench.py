@@ -741,7 +741,7 @@ def copy_ceiling(n=256, fields=15, iters=40, prec="f32"):
     return out
 
 
-def dispatch_gaps(trace_csv, kernel="k_march_batch", round_trip_ns=200000):
+def dispatch_gaps(trace_csv, kernel="k_brick_batch<", round_trip_ns=200000):
     """Idle time between consecutive dispatches of the batched step kernel in
     a rocprofv3 kernel trace (CSV).  Dispatches closer than round_trip_ns
     belong to one lq_batch_step call (launches queued back to back); a longer

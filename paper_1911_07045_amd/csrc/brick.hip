@@ -2,7 +2,7 @@
 //
 // A small box does not fill the GPU, so its step lasts as long as one block's
 // chain of dependent waits, not as long as its bytes take.  A marching block
-// (kernels.hip) waits for memory once per plane; here a block owns one
+// (march.h) waits for memory once per plane; here a block owns one
 // X x Y x Z brick with one thread per site, loads the brick and its one-site
 // halo at once (each thread its own site and IPT halo sites), drifts them into
 // LDS and evaluates the force after a single barrier.  The controller of the
