@@ -446,8 +446,10 @@ __device__ bool dc_begin(FireDev* st, const double* partials, int nblocks, int k
 // is the lattice's own tile count; partials are indexed by tile, so the
 // reduction order does not depend on how blocks are dispatched.  The
 // controller of step k - 1 runs at the start (dc_begin); the partials of
-// step k go to slot k & 1.
-template <typename T, bool L23, bool L4, int MODE, int W, bool ROWS>
+// step k go to slot k & 1.  BATCH: L4 says only that members may be chiral;
+// one that is not marches in the direction that its kernel alone takes, since
+// the order of a block's sums follows the march.
+template <typename T, bool L23, bool L4, int MODE, int W, bool ROWS, bool BATCH = false>
 __device__ __forceinline__ void step_block(const LatDev& L, const Bufs<T>& b, const T* __restrict__ qin,
                                            T* __restrict__ Fout, double* partials, FireDev* st,
                                            int nblocks, int bid, int k) {
@@ -468,7 +470,8 @@ __device__ __forceinline__ void step_block(const LatDev& L, const Bufs<T>& b, co
     if (STEP) {
         if (dc_begin(st, partials, nblocks, k, bid, scratch, ctl_d, ctl_i)) return;
         const int cur = ctl_i[0] & 1;
-        down = !(L4 && sizeof(T) == 8) && (ctl_i[0] & 2) != 0;
+        const bool upwards = L4 && sizeof(T) == 8 && (!BATCH || L.L4 != 0.0);
+        down = !upwards && (ctl_i[0] & 2) != 0;
         const double dtd = ctl_d[0], c_v = ctl_d[1], c_F = ctl_d[2], mu = ctl_d[3];
         // selects rather than indexing by cur, which would put b in scratch
         q_in = cur ? b.q[1] : b.q[0]; v_in = cur ? b.v[1] : b.v[0]; F_in = cur ? b.F[1] : b.F[0];
@@ -539,7 +542,7 @@ __global__ __launch_bounds__((Tile<T, L23, W>::N)) __attribute__((amdgpu_waves_p
         b.q[i] = (T*)M.q[i]; b.v[i] = (T*)M.v[i]; b.F[i] = (T*)M.F[i];
     }
     const LatDev& L = M.L;
-    step_block<T, L23, L23, MODE_FIRE, W, true>(L, b, nullptr, nullptr, M.partials, M.st, M.nblocks,
+    step_block<T, L23, L23, MODE_FIRE, W, true, true>(L, b, nullptr, nullptr, M.partials, M.st, M.nblocks,
                                           (int)blockIdx.x - off[m], k);
 }
 

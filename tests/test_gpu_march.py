@@ -1,0 +1,88 @@
+"""The marching kernels: batches, minimizers, stops, resumes and divergence on
+lattices above the sizes that step in bricks.
+"""
+import numpy as np
+import pytest
+
+from paper_1911_07045_amd import lqfire, synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+ELASTIC = {"one": {}, "l23": dict(L2=1.16, L3=0.7), "chiral": dict(L2=0.9, L3=1.16, L4=-0.6)}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    lqfire.lib()
+
+
+def _objects(shape):
+    nx, ny, nz = shape
+    return [dict(kind="sphere", center=(nx * 0.4, ny * 0.6, nz * 0.5), radius=min(shape) / 6.0 + 0.3, law="rp", W=3.0,
+                 dir="normal"),
+            dict(kind="wall", axis=2, plane=nz - 1, law="fg", W=0.7)]
+
+
+def _lattice(shape, prec, elastic, periodic=(True, True, True)):
+    lat = lqfire.Lattice(shape, periodic, prec, L1=2.32, **ELASTIC[elastic])
+    lat.set_boundaries(_objects(shape))
+    return lat
+
+
+def _dev(a, dtype):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(device="cuda", dtype=dtype).contiguous()
+
+
+def _random_start(lat, seed=5):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    d = torch.randn(3, lat.N, generator=g, device="cuda", dtype=torch.float64)
+    return lat.set_uniaxial(d / d.norm(dim=0), lat.empty())
+
+
+def _fire(shape, prec, elastic, seed=5):
+    lat = _lattice(shape, prec, elastic)
+    q, v, F = _random_start(lat, seed), lat.empty(), lat.empty()
+    lat.fire_init(lqfire.make_fire_params(force_tol=0.0, max_steps=10 ** 6), q, v, F)
+    return lat, q, v, F
+
+
+# precision, members (elastic terms, shape): narrow and wide marching tiles and
+# a box that steps in bricks; L2/L3 and chiral members share a batch
+BATCHES = [
+    ("f64", [("l23", (64, 84, 90)), ("chiral", (64, 80, 90)), ("l23", (61, 96, 90)), ("chiral", (60, 92, 84)), ("l23", (24, 20, 18))]),
+    ("f64", [("one", (64, 84, 80)), ("one", (61, 96, 90)), ("one", (24, 20, 18))]),
+    ("f32", [("l23", (64, 80, 84)), ("chiral", (64, 76, 84)), ("l23", (61, 80, 90)), ("chiral", (60, 84, 84)), ("l23", (24, 20, 18))]),
+]
+
+
+@pytest.mark.parametrize("prec,members", BATCHES, ids=["f64_l23", "f64_one", "f32_l23"])
+def test_batch_equals_alone_bitwise(prec, members):
+    """A member follows its solo trajectory bit for bit, sums and steering
+    included, over calls of odd and even length.  (Sums taken in another order
+    differ in the last bit of a total only now and then, hence the many steps.)"""
+    alone = []
+    for i, (elastic, shape) in enumerate(members):
+        print(f"[march] alone {prec} {elastic} {shape}", flush=True)
+        lat, *fields = _fire(shape, prec, elastic, seed=5 + i)
+        rep = lat.fire_step(403)
+        alone.append(([f.clone() for f in fields], rep.as_dict()))
+        lat.close()
+    b = lqfire.Batch(len(members))
+    held = [_fire(shape, prec, elastic, seed=5 + i) for i, (elastic, shape) in enumerate(members)]
+    for h in held:
+        b.add(h[0])
+    print(f"[march] batch {prec}", flush=True)
+    for n in (5, 201, 130, 67):
+        reps = b.step(n)
+    for (lat, *fields), (ref, rep_a), rep in zip(held, alone, reps):
+        assert rep.as_dict() == rep_a
+        assert all(torch.equal(x, y) for x, y in zip(fields, ref))
+    b.close()
+    for h in held:
+        h[0].close()
