@@ -347,16 +347,25 @@ int32_t lq_batch_size(const lq_batch* b);
  * of the rest).  Synchronizes the batch stream. */
 int lq_batch_step(lq_batch* b, int64_t n_steps, lq_fire_report* reports);
 
-/* ---- work plan of the step kernels (host only) ----
- * How the marching kernels split the fused step (Algorithm 1 over the whole
- * lattice) into blocks (small lattices step in bricks instead, one thread per
- * site and one brick per block, and take from this plan only which FP32 planes
- * use the bulk form of the force) for a lattice with the given parameters and objects (as
- * lq_set_boundaries would rasterize them, without records or extra object
- * sites) on a device that keeps `resident` step blocks resident at once
- * (> 0).  A chunk is the X x Y column tile whose first site is (x0, y0), over
- * the planes z0 .. z0 + zc - 1; a block marches one chunk, or two one after
- * the other.  Writes up to cap chunks as 4 int32 each {x0, y0, z0, zc} into
+/* ---- step kernels and their work plan (host only) ----
+ * Which kernels advance a lattice with the given parameters (Algorithm 1, the
+ * descents, and the force alone): small lattices step in bricks, one thread
+ * per site and one brick per block; larger ones in marching blocks on narrow
+ * or wide column tiles.  Needs no GPU.  LQ_EINVAL on bad parameters or kind
+ * NULL. */
+#define LQ_STEP_NARROW 0
+#define LQ_STEP_WIDE 1
+#define LQ_STEP_BRICKS 2
+int lq_step_kind(const lq_params* p, int32_t* kind);
+
+/* How the marching kernels split the fused step (Algorithm 1 over the whole
+ * lattice) into blocks, for a lattice with the given parameters and objects
+ * (as lq_set_boundaries would rasterize them, without records or extra object
+ * sites; a lattice that steps in bricks takes from this plan only which FP32
+ * planes use the bulk form of the force), on a device that keeps `resident`
+ * step blocks resident at once (> 0).  A chunk is the X x Y column tile whose
+ * first site is (x0, y0), over the planes z0 .. z0 + zc - 1; a block marches
+ * one chunk, or two one after the other.  Writes up to cap chunks as 4 int32 each {x0, y0, z0, zc} into
  * chunks, one byte each into bulk (1: every site of the tile, its one-site
  * ring and the planes z0 - 1 and z0 + zc is simulated with all six
  * neighbours) and, if block is not NULL, the index of the block that marches

@@ -497,6 +497,11 @@ static bool bricks_for(const lq_params& p, bool l23) {
     return N * std::max(0.6, N / marched) <= most && (nb <= 256 || 2.0 * N >= (double)(nb * S[0] * S[1] * S[2]));
 }
 
+// The kernels that step a lattice (KIND_*).
+static int step_kind_for(const lq_params& p, bool l23) {
+    return bricks_for(p, l23) ? (int)KIND_BRICK : tile_wide_for(p.n[0], p.prec, l23);
+}
+
 // The bricks of a lattice, x fastest: bit z of a brick's byte is set when the
 // sites of its plane z take the bulk form of the force.  FP64: when the padded
 // planes z - 1 .. z + 1 are all full bulk sites.  FP32: when the marching plan
@@ -587,18 +592,17 @@ static int upload_geometry(lq_lattice* lat, const Geometry& g) {
     d.N = lat->N;
     d.A = p.A; d.B = p.B; d.C = p.C; d.L1 = p.L1; d.L2 = p.L2; d.L3 = p.L3; d.L4 = p.L4;
     ChunkPlan plan;
-    if (bricks_for(p, lat->l23)) {
+    d.kind = step_kind_for(p, lat->l23);
+    if (d.kind == KIND_BRICK) {
         int64_t S[3];
         brick_size(lat->l23, S);
         const uint64_t nbx = (uint64_t)((p.n[0] + S[0] - 1) / S[0]), nby = (uint64_t)((p.n[1] + S[1] - 1) / S[1]);
-        d.kind = KIND_BRICK;
         d.two_waves = 0;
         d.magic_x = ((uint64_t)1 << 32) / nbx + 1;
         d.magic_xy = ((uint64_t)1 << 32) / (nbx * nby) + 1;
         plan.bulk = plan_bricks(p, lat->l23, g.mask, lat->device);
         d.nblocks = (int)plan.bulk.size();
     } else {
-        d.kind = tile_wide_for(p.n[0], p.prec, lat->l23);
         d.two_waves = two_waves_for(p, lat->device, lat->l23, d.kind) ? 1 : 0;
         plan_chunks(p, lat->l23, d.kind, g.mask, resident_blocks(p, lat->device, lat->l23, d.kind, d.two_waves != 0),
                     plan);
@@ -738,6 +742,16 @@ int lq_rasterize(const lq_params* p, const lq_object* objs, int32_t n_objs, cons
         anch_site[i] = g.anch_site[i];
         std::memcpy(anch_data + ANCH_STRIDE * i, &g.anch_data[ANCH_STRIDE * i], ANCH_STRIDE * sizeof(double));
     }
+    return LQ_OK;
+}
+
+int lq_step_kind(const lq_params* p, int32_t* kind) {
+    std::string err;
+    const int rc = check_params(p, err);
+    if (rc != LQ_OK) return fail(nullptr, rc, err);
+    if (!kind) return fail(nullptr, LQ_EINVAL, "kind is NULL");
+    static_assert(KIND_NARROW == LQ_STEP_NARROW && KIND_WIDE == LQ_STEP_WIDE && KIND_BRICK == LQ_STEP_BRICKS, "");
+    *kind = step_kind_for(*p, p->L2 != 0.0 || p->L3 != 0.0 || p->L4 != 0.0);
     return LQ_OK;
 }
 

@@ -135,6 +135,7 @@ def lib():
                                               C.POINTER(MinResult)]),
             "lq_director_field": (C.c_int, [vp, vp, vp, vp, vp, C.c_double, C.POINTER(C.c_int64)]),
             "lq_stream_copy": (C.c_int, [C.POINTER(vp), C.POINTER(vp), i32, i64, i32, vp]),
+            "lq_step_kind": (C.c_int, [C.POINTER(Params), C.POINTER(i32)]),
             "lq_step_plan": (C.c_int, [C.POINTER(Params), C.POINTER(Object), i32, i64, C.POINTER(C.c_int32),
                                        C.POINTER(C.c_uint8), C.POINTER(C.c_int32), i64, C.POINTER(C.c_int64),
                                        C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
@@ -476,6 +477,15 @@ class Batch:
         if rc not in (LQ_OK, LQ_ENONFINITE):
             _check(rc)
         return [reps[i] for i in range(n)]
+
+
+def step_kind(shape, periodic=(True, True, True), prec="f64", A=-0.172, B=-2.12, C_=1.73, L1=2.32, L2=0.0,
+              L3=0.0, L4=0.0):
+    """lq_step_kind (host only): "bricks", or "narrow" or "wide" marching tiles."""
+    p = make_params(shape, periodic, prec, A, B, C_, L1, L2, L3, L4)
+    kind = C.c_int32()
+    _check(lib().lq_step_kind(C.byref(p), C.byref(kind)))
+    return ("narrow", "wide", "bricks")[kind.value]
 
 
 def step_plan(shape, periodic=(True, True, True), prec="f64", objects=(), resident=256, A=-0.172, B=-2.12,
