@@ -664,7 +664,9 @@ __device__ __forceinline__ void sum_partials(const double* partials, int nblocks
 
 // After the k_steps step kernels of a call: the controller on the last
 // step's reduction (the same sums, in the same order, as in a step kernel
-// of NT threads; its first `stride` threads sum), or the state the run stopped with, into st[0].
+// of NT threads; its first `stride` threads sum), or the state the run
+// stopped with, into st[0].  Every wave reads the stop word, so it stays as it
+// is here: the start of the next call clears it.
 template <int NT>
 __device__ __forceinline__ void dc_final(FireDev* st, const double* partials, int nblocks, int k_steps,
                                          double (*scratch)[4], int stride = NT) {
@@ -673,7 +675,6 @@ __device__ __forceinline__ void dc_final(FireDev* st, const double* partials, in
         if (threadIdx.x == 0) {
             const int sl = ctl->slot;
             if (sl != 0) st[0] = st[sl];
-            ctl->halt = 0;
         }
         return;
     }

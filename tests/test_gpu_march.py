@@ -86,3 +86,52 @@ def test_batch_equals_alone_bitwise(prec, members):
     b.close()
     for h in held:
         h[0].close()
+
+
+# precision, elastic terms, shape: marching tiles of both widths, and boxes of
+# up to 256 bricks (controller in one wave), above 256 (in the block) and above
+# one brick per thread of a block
+STOPS = [("f64", "l23", (64, 84, 90)), ("f64", "one", (61, 96, 90)), ("f64", "chiral", (60, 92, 84)),
+         ("f32", "one", (128, 96, 90)), ("f32", "l23", (61, 80, 90)), ("f32", "one", (24, 20, 18)),
+         ("f64", "l23", (44, 40, 40)), ("f32", "one", (66, 64, 64))]
+
+
+def _start(prec, elastic, shape, method, tol=0.0, cap=10 ** 6):
+    lat = _lattice(shape, prec, elastic)
+    q, v, F = _random_start(lat), lat.zeros(), lat.empty()
+    if method == "fire":
+        lat.fire_init(lqfire.make_fire_params(force_tol=tol, max_steps=cap), q, v, F)
+    else:
+        mu = 0.8 if method == "nesterov" else 0.0
+        lat.descent_init(lqfire.make_descent_params(method, 2e-3, mu, force_tol=tol, max_steps=cap), q, v, F)
+    return lat, q, v, F
+
+
+@pytest.mark.parametrize("method", ["fire", "gd", "nesterov"])
+@pytest.mark.parametrize("prec,elastic,shape", STOPS)
+def test_stop_inside_a_call(prec, elastic, shape, method):
+    """A run that stops inside one call, by its tolerance or its step limit,
+    has the state and report of the same run taken one step per call; the
+    kernels after the stop, and later calls, change nothing."""
+    print(f"[march] stop {prec} {elastic} {shape} {method}", flush=True)
+    lat, *_ = _start(prec, elastic, shape, method)
+    tol = lat.fire_step(40).maxF * (1.0 + 1e-12)  # reached after 40 steps at the latest
+    lat.close()
+    for tol, cap in ((tol, 10 ** 6), (0.0, 17), (0.0, 18)):
+        out = []
+        for n in (90, 1):
+            lat, *fields = _start(prec, elastic, shape, method, tol, cap)
+            rep = lat.fire_step(n)
+            while n == 1 and rep.status == lqfire.RUNNING and rep.step < 90:
+                rep = lat.fire_step(1)
+            state = [f.clone() for f in fields]
+            for more in (3, 0, 30):
+                assert lat.fire_step(more).as_dict() == rep.as_dict()
+            assert all(torch.equal(a, b) for a, b in zip(state, fields))
+            out.append((rep.as_dict(), state))
+            lat.close()
+        assert out[0][0] == out[1][0]
+        assert all(torch.equal(a, b) for a, b in zip(out[0][1], out[1][1]))
+        rep = out[0][0]
+        assert (rep["status"] == lqfire.CONVERGED and 0 < rep["step"] <= 40) if tol else \
+            (rep["status"] == lqfire.MAX_STEPS and rep["step"] == cap)

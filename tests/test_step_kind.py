@@ -43,6 +43,8 @@ def test_boxes_of_the_gpu_tests():
         got = {(elastic, kind(shape, prec, elastic)) for elastic, shape in members}
         terms = {e for e, _ in members}
         assert got >= {(e, k) for e in terms for k in ("narrow", "wide")} and "bricks" in {k for _, k in got}
+    got = {(prec, kind(shape, prec, elastic)) for prec, elastic, shape in test_gpu_march.STOPS}
+    assert got == {(p, k) for p in ("f32", "f64") for k in ("narrow", "wide", "bricks")}
 
 
 def test_bad_arguments():
