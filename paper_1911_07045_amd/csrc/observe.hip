@@ -17,20 +17,33 @@ namespace lq {
 // (256^3 FP32 one-constant 440 -> 146 us per call, where its 336 MB take 68;
 // L2/L3 578 -> 221; 128^3 110 -> 41, of which 20 are two launches and a wait);
 // loading the neighbours one plane ahead measured equal to 15% slower, 2048 or
-// 8192 blocks instead of 4096 equal or slower.  A thread owns one column (x, y) of the plane and walks ENERGY planes
-// upwards with the own and the next plane's q in registers.  Bonds are taken
+// 8192 blocks instead of 4096 equal or slower.  A thread owns one column (x, y)
+// and walks zc planes of it upwards with the own and the next plane's q in
+// registers.  A block takes 256 columns of one run of planes, or (PACKED) the
+// columns' runs follow each other over the threads: boxes of few columns would
+// leave most of such blocks idle (3x3x100000 FP32 207 us, packed 32; L2/L3 280
+// and 40; 4x4x30000 77 and 26), while in full blocks z is uniform (256^3 FP32
+// 145.9, packed 147.0).  Bonds are taken
 // once, from their lower end, with the weights of both ends (1/n_k each, 1/2
 // in the bulk); the cross-axis and chiral terms need the mean differences of
 // the site and so both neighbours of every axis.
-template <typename T, bool L23>
+template <typename T, bool L23, bool PACKED>
 __global__ __launch_bounds__(256) void k_energy(LatDev L, const T* __restrict__ q, int zc, double* partials) {
     __shared__ double scratch[4][4];
     const int nxy = L.nx * L.ny;
-    const int nblocks = (int)(gridDim.x * gridDim.y);
-    const int bid = xcd_block((int)(blockIdx.x + gridDim.x * blockIdx.y), nblocks);
-    const int p = (bid % (int)gridDim.x) * 256 + (int)threadIdx.x;
-    const int z0 = (bid / (int)gridDim.x) * zc, z1 = min(z0 + zc, L.nz);
-    const bool own = p < nxy;
+    const int bid = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    int run, p;
+    if (PACKED) {
+        const int item = bid * 256 + (int)threadIdx.x;
+        run = item / nxy;
+        p = item - run * nxy;
+    } else {
+        const int cols = (nxy + 255) / 256;
+        run = bid / cols;
+        p = (bid - run * cols) * 256 + (int)threadIdx.x;
+    }
+    const int z0 = run * zc, z1 = min(z0 + zc, L.nz);
+    const bool own = p < nxy && z0 < L.nz;
     const int x = p % L.nx, y = p / L.nx;
     const uint32_t cs = (uint32_t)L.N * (uint32_t)sizeof(T);
     const __amdgpu_buffer_rsrc_t rq = field_rsrc(q, 5u * cs);
@@ -353,22 +366,29 @@ __global__ __launch_bounds__(256) void k_count_sum(const uint32_t* counts, int n
 // ---------------------------------------------------------------------------
 // launchers
 
-// Blocks of the energy kernel: 256 columns each, in runs of zc planes so short
-// that some 4096 blocks share the lattice (small lattices: one plane a block).
-static int energy_planes(const LatDev& L) {
-    const int64_t cols = ((int64_t)L.nx * L.ny + 255) / 256;
-    return (int)((cols * L.nz + 4095) / 4096);
-}
-static int64_t n_energy_parts(const LatDev& L) {
-    const int64_t cols = ((int64_t)L.nx * L.ny + 255) / 256;
-    const int zc = energy_planes(L);
-    return cols * ((L.nz + zc - 1) / zc);
+// Work split of the energy kernel: runs of zc planes of a column, so short that
+// some 4096 blocks share the lattice (small ones: one plane a run); packed where
+// blocks of 256 columns would leave more than a fifth of their threads idle.
+struct EnergySplit {
+    bool packed;
+    int zc;
+    int64_t blocks;
+};
+static EnergySplit energy_split(const LatDev& L) {
+    const int64_t nxy = (int64_t)L.nx * L.ny, cols = (nxy + 255) / 256;
+    EnergySplit e;
+    e.packed = 4 * 256 * cols > 5 * nxy;
+    const int64_t threads = (e.packed ? nxy : 256 * cols) * L.nz;
+    e.zc = (int)std::min<int64_t>((threads + 4096 * 256 - 1) / (4096 * 256), L.nz);
+    const int64_t runs = (L.nz + e.zc - 1) / e.zc;
+    e.blocks = e.packed ? (nxy * runs + 255) / 256 : cols * runs;
+    return e;
 }
 
 // Blocks of the director kernel (a grid-stride loop over the sites).
 static int director_blocks(const LatDev& L) { return (int)std::min<int64_t>((L.N + 255) / 256, 4096); }
 int64_t n_observe_bytes(const LatDev& L) {
-    return std::max<int64_t>(n_energy_parts(L) * 4 * (int64_t)sizeof(double), director_blocks(L) * (int64_t)sizeof(uint32_t));
+    return std::max<int64_t>(energy_split(L).blocks * 4 * (int64_t)sizeof(double), director_blocks(L) * (int64_t)sizeof(uint32_t));
 }
 
 int launch_directors(const LatDev& L, int prec, const void* q, void* dirs, void* lmax, uint8_t* defect,
@@ -385,20 +405,25 @@ int launch_directors(const LatDev& L, int prec, const void* q, void* dirs, void*
     return hipGetLastError() == hipSuccess ? LQ_OK : LQ_EHIP;
 }
 
+template <typename T, bool L23>
+static void energy_t(const LatDev& L, const EnergySplit& e, const void* q, double* partials, hipStream_t s) {
+    if (e.packed) k_energy<T, L23, true><<<dim3((unsigned)e.blocks), 256, 0, s>>>(L, (const T*)q, e.zc, partials);
+    else k_energy<T, L23, false><<<dim3((unsigned)e.blocks), 256, 0, s>>>(L, (const T*)q, e.zc, partials);
+}
+
 int launch_energy(const LatDev& L, bool l23, int prec, const void* q, double* partials, EnergyOut* out,
                   void* stream) {
     hipStream_t s = (hipStream_t)stream;
-    const int zc = energy_planes(L);
-    const dim3 g((unsigned)(((int64_t)L.nx * L.ny + 255) / 256), (unsigned)((L.nz + zc - 1) / zc));
+    const EnergySplit e = energy_split(L);
     if (prec == LQ_F64) {
-        if (l23) k_energy<double, true><<<g, 256, 0, s>>>(L, (const double*)q, zc, partials);
-        else k_energy<double, false><<<g, 256, 0, s>>>(L, (const double*)q, zc, partials);
+        if (l23) energy_t<double, true>(L, e, q, partials, s);
+        else energy_t<double, false>(L, e, q, partials, s);
     } else {
-        if (l23) k_energy<float, true><<<g, 256, 0, s>>>(L, (const float*)q, zc, partials);
-        else k_energy<float, false><<<g, 256, 0, s>>>(L, (const float*)q, zc, partials);
+        if (l23) energy_t<float, true>(L, e, q, partials, s);
+        else energy_t<float, false>(L, e, q, partials, s);
     }
     if (hipGetLastError() != hipSuccess) return LQ_EHIP;
-    k_energy_sum<<<1, SUM_THREADS, 0, s>>>(partials, (int)n_energy_parts(L), out);
+    k_energy_sum<<<1, SUM_THREADS, 0, s>>>(partials, (int)e.blocks, out);
     return hipGetLastError() == hipSuccess ? LQ_OK : LQ_EHIP;
 }
 
