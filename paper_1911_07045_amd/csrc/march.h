@@ -104,10 +104,11 @@ __device__ __forceinline__ void ring_pos(int r, int& px, int& py) {
     else { px = PX - 1; py = r - 2 * PX - (PY - 2) + 1; }
 }
 
-// Positions of a tile that hangs over the box's edge: the step kernels with L4
-// load nothing there (SKIP; FP64 101x90x67 74.7 -> 71.9 us per step), the others
+// Positions of a tile that hangs over the box's edge: the FP64 step kernels with
+// L4 load nothing there (SKIP; 101x90x67 74.7 -> 71.9 us per step), the others
 // a wrapped site (FP32 one-constant 230x187x141 202 us, 218 without; FP32 L2/L3
-// and the force alone 2-3% faster too).
+// and the force alone 2-3% faster too; FP32 with L4, FIRE and gradient descent:
+// 201x163x95 172 and 121, 181 and 136 without; 24x400x400 290, 318 without).
 template <bool SKIP>
 __device__ __forceinline__ int wrapt(int g, int n, int per) { return SKIP ? wrap1(g, n, per) : wrapc(g, n, per); }
 
@@ -140,7 +141,7 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
     constexpr bool STEP = MODE != MODE_FORCE;
     constexpr bool USES_V = MODE == MODE_FIRE || MODE == MODE_NAG;
     constexpr bool ZERO_SOLID = !BULK && L23 && branch_free<T>();
-    constexpr bool SKIP = L4 && STEP;
+    constexpr bool SKIP = L4 && STEP && sizeof(T) == 8;
     const int64_t N = L.N;
     const int nxy = L.nx * L.ny;
     const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
