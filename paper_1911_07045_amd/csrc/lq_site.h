@@ -60,7 +60,7 @@ __device__ __forceinline__ void bst_p(__amdgpu_buffer_rsrc_t r, uint32_t voff, u
 template <typename T, bool L23, bool ROWS>
 constexpr int store_policy() { return (L23 && sizeof(T) == 4) || !ROWS ? 0 : 2; }
 template <typename T>
-inline bool state_fits_cache(int64_t N) { return 2 * 15 * N * (int64_t)sizeof(T) <= (int64_t)256 << 20; }
+__host__ __device__ inline bool state_fits_cache(int64_t N) { return 2 * 15 * N * (int64_t)sizeof(T) <= (int64_t)256 << 20; }
 template <typename T>
 inline bool whole_rows(int nx) { return ((size_t)nx * sizeof(T)) % 64 == 0; }
 

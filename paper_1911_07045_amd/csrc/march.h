@@ -93,8 +93,11 @@ struct Stencil {
 // holds them.  That pays where the state is stored with the default policy (us
 // per step, FP32 L2/L3 201x163x95 slab 145.7 -> 134.3, 256^3 437 -> 426;
 // one-constant 230x187x141 FP32 198 -> 181, FP64 371 -> 361) and is neutral
-// with the non-temporal one.  The FP64 L4 kernels march upwards always
-// (201x163x95 with a colloid 358, in turn 363).
+// with the non-temporal one.  Upwards always march the FP64 L4 kernels
+// (201x163x95 with a colloid 358, in turn 363) and the L2/L3 kernels of narrow
+// tiles (FP64 24x400x400 508, in turn 517, gradient descent 481 and 495; FP32
+// 3x64x4000 297 and 316, 60x300x300 211 and 216) and of state that stays in the
+// cache either way (FP32 L4 150x100x100 75.8 and 78.7, 130x140x70 72.4 and 74.8).
 template <typename T, bool L23, int W>
 __device__ __forceinline__ void ring_pos(int r, int& px, int& py) {
     constexpr int PX = Tile<T, L23, W>::PX, PY = Tile<T, L23, W>::PY;
@@ -471,7 +474,8 @@ __device__ __forceinline__ void step_block(const LatDev& L, const Bufs<T>& b, co
     if (STEP) {
         if (dc_begin(st, partials, nblocks, k, bid, scratch, ctl_d, ctl_i)) return;
         const int cur = ctl_i[0] & 1;
-        const bool upwards = L4 && sizeof(T) == 8 && (!BATCH || L.L4 != 0.0);
+        const bool upwards = (L23 && (W == 0 || state_fits_cache<T>(L.N))) ||
+                             (L4 && sizeof(T) == 8 && (!BATCH || L.L4 != 0.0));
         down = !upwards && (ctl_i[0] & 2) != 0;
         const double dtd = ctl_d[0], c_v = ctl_d[1], c_F = ctl_d[2], mu = ctl_d[3];
         // selects rather than indexing by cur, which would put b in scratch

@@ -53,15 +53,18 @@ def _fire(shape, prec, elastic, seed=5):
 
 
 # precision, members (elastic terms, shape): narrow and wide marching tiles and
-# a box that steps in bricks; L2/L3 and chiral members share a batch
+# a box that steps in bricks; L2/L3 and chiral members share a batch; the second
+# and the last batch hold boxes beyond the cache, whose steps march both ways
 BATCHES = [
     ("f64", [("l23", (64, 84, 90)), ("chiral", (64, 80, 90)), ("l23", (61, 96, 90)), ("chiral", (60, 92, 84)), ("l23", (24, 20, 18))]),
+    ("f64", [("l23", (64, 132, 140)), ("chiral", (64, 132, 140)), ("l23", (61, 140, 150)), ("chiral", (61, 96, 100)), ("l23", (24, 20, 18))]),
     ("f64", [("one", (64, 84, 80)), ("one", (61, 96, 90)), ("one", (24, 20, 18))]),
     ("f32", [("l23", (64, 80, 84)), ("chiral", (64, 76, 84)), ("l23", (61, 80, 90)), ("chiral", (60, 84, 84)), ("l23", (24, 20, 18))]),
+    ("f32", [("l23", (64, 192, 190)), ("chiral", (64, 192, 190)), ("l23", (61, 80, 90)), ("chiral", (60, 84, 84)), ("l23", (24, 20, 18))]),
 ]
 
 
-@pytest.mark.parametrize("prec,members", BATCHES, ids=["f64_l23", "f64_one", "f32_l23"])
+@pytest.mark.parametrize("prec,members", BATCHES, ids=["f64_l23", "f64_l23_large", "f64_one", "f32_l23", "f32_l23_large"])
 def test_batch_equals_alone_bitwise(prec, members):
     """A member follows its solo trajectory bit for bit, sums and steering
     included, over calls of odd and even length.  (Sums taken in another order
