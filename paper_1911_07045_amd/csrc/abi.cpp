@@ -2,7 +2,8 @@
 //
 // The handle owns the geometry tables on the device (neighbour masks, tile
 // flags, anchoring sums) and small scratch for the energy sum and defect count.  The caller
-// owns every field buffer and the FIRE workspace.
+// owns every field buffer and the FIRE workspace; steps in bricks keep their
+// block partials with the handle.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -54,7 +55,8 @@ struct lq_lattice {
     void* F = nullptr;
     Bufs<double> b64{};
     Bufs<float> b32{};
-    double* d_partials = nullptr;
+    double* d_partials = nullptr;       // workspace: block partials of the initial reduction and of marching steps
+    double* d_brick_partials = nullptr; // steps in bricks: theirs, behind the scratch in d_observe
     FireDev* d_state = nullptr;
     FireDev *h_state = nullptr, *d_hstate = nullptr;  // pinned, and its device address
     LatDev dev{};
@@ -562,6 +564,24 @@ static std::vector<uint8_t> plan_bricks(const lq_params& p, bool l23, const std:
     return bits;
 }
 
+static int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
+
+// Two slots of block partials: step k writes slot k & 1 while step k + 1 reads
+// the other one.
+static int64_t partials_bytes(int64_t slots) { return align256(2 * slots * 4 * (int64_t)sizeof(double)); }
+
+// Block partials that the workspace holds: of the initial reduction, and of
+// marching steps.  Small lattices may have more bricks than that; the partials
+// of their steps belong to the handle, so that a workspace needs no more for
+// them than a marching lattice's.
+static int64_t partial_slots(const lq_lattice* lat) {
+    const int64_t init = n_energy_blocks(lat->dev);
+    return lat->dev.kind == KIND_BRICK ? init : std::max<int64_t>(n_step_blocks(lat->dev), init);
+}
+static double* step_partials(const lq_lattice* lat) {
+    return lat->dev.kind == KIND_BRICK ? lat->d_brick_partials : lat->d_partials;
+}
+
 static void free_geometry(lq_lattice* lat) {
     if (lat->d_mask) (void)hipFree(lat->d_mask);
     if (lat->d_tile) (void)hipFree(lat->d_tile);
@@ -686,7 +706,9 @@ int lq_lattice_create(const lq_params* p, void* stream, lq_lattice** out) {
     rc = rasterize(lat->p, lat->S0, nullptr, 0, nullptr, 0, nullptr, 0, g, err);
     if (rc == LQ_OK) rc = upload_geometry(lat, g);
     if (rc == LQ_OK) {
-        if (hipMalloc(&lat->d_observe, (size_t)n_observe_bytes(lat->dev)) != hipSuccess ||
+        const int64_t observe = align256(n_observe_bytes(lat->dev));
+        const int64_t bricks = lat->dev.kind == KIND_BRICK ? partials_bytes(n_step_blocks(lat->dev)) : 0;
+        if (hipMalloc(&lat->d_observe, (size_t)(observe + bricks)) != hipSuccess ||
             hipHostMalloc(&lat->h_eout, sizeof(EnergyOut), hipHostMallocDefault) != hipSuccess ||
             hipHostGetDevicePointer((void**)&lat->d_eout, lat->h_eout, 0) != hipSuccess ||
             hipHostMalloc(&lat->h_state, sizeof(FireDev), hipHostMallocDefault) != hipSuccess ||
@@ -697,6 +719,7 @@ int lq_lattice_create(const lq_params* p, void* stream, lq_lattice** out) {
             err = "device allocation failed";
             rc = LQ_ENOMEM;
         }
+        if (rc == LQ_OK && bricks > 0) lat->d_brick_partials = (double*)((char*)lat->d_observe + observe);
     } else if (err.empty()) {
         err = lat->err;
     }
@@ -888,17 +911,8 @@ int lq_director_field(lq_lattice* lat, const void* q, void* dirs, void* lambda_m
     return LQ_OK;
 }
 
-static int64_t partial_slots(const lq_lattice* lat) {
-    return std::max<int64_t>(n_step_blocks(lat->dev), n_energy_blocks(lat->dev));
-}
-
-static int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
-
-// Workspace: the second buffer of q, v and F; two slots of block partials
-// (step k writes slot k & 1 while step k + 1 reads it); the controller
+// Workspace: the second buffer of q, v and F; block partials; the controller
 // state st[2] and its DcCtl word.
-static int64_t partials_bytes(int64_t slots) { return align256(2 * slots * 4 * (int64_t)sizeof(double)); }
-
 int64_t lq_workspace_bytes(const lq_lattice* lat) {
     if (!lat) return -1;
     const int64_t field = align256(5 * lat->N * (int64_t)elem_size(lat));
@@ -1069,7 +1083,7 @@ int lq_fire_step(lq_lattice* lat, int64_t n_steps, lq_fire_report* out) {
     HIPCHK(lat, hipSetDevice(lat->device));
     const void* bufs = lat->p.prec == LQ_F64 ? (const void*)&lat->b64 : (const void*)&lat->b32;
     int rc = launch_begin(lat->d_state, n_steps, lat->stream);
-    if (rc == LQ_OK) rc = launch_fire_steps(lat->dev, lat->l23, lat->p.prec, lat->method, bufs, lat->d_partials,
+    if (rc == LQ_OK) rc = launch_fire_steps(lat->dev, lat->l23, lat->p.prec, lat->method, bufs, step_partials(lat),
                                             lat->d_state, n_steps, lat->stream);
     if (rc == LQ_OK)
         rc = launch_finalize(lat->dev, lat->p.prec, lat->method != LQ_METHOD_GD, bufs, lat->d_state, lat->d_hstate,
@@ -1124,10 +1138,7 @@ int lq_minimize_noalloc(lq_lattice* lat, const lq_fire_params* fp, void* q, void
                         lq_min_result* out) {
     if (!lat) return fail(nullptr, LQ_EINVAL, "lattice is NULL");
     lat->bound = false;
-    // the limit counts one partial-sum slot per 256 sites (lattices in bricks
-    // may hold more; the array has room for them on top of its size)
-    const int64_t need = lq_workspace_bytes(lat) - partials_bytes(partial_slots(lat)) +
-                         partials_bytes(lat->dev.kind == KIND_BRICK ? n_energy_blocks(lat->dev) : partial_slots(lat));
+    const int64_t need = lq_workspace_bytes(lat);
     if (need > LQ_NOALLOC_WORKSPACE_BYTES) {
         char msg[192];
         std::snprintf(msg, sizeof msg,
@@ -1140,7 +1151,7 @@ int lq_minimize_noalloc(lq_lattice* lat, const lq_fire_params* fp, void* q, void
     void* ws = nullptr;
     int rc = noalloc_workspace(lat->device, &ws);
     if (rc != LQ_OK) return fail(lat, rc, "device address of the fixed workspace not available");
-    rc = lq_fire_init(lat, fp, q, v, F, ws, NOALLOC_ARRAY_BYTES, nullptr);
+    rc = lq_fire_init(lat, fp, q, v, F, ws, LQ_NOALLOC_WORKSPACE_BYTES, nullptr);
     if (rc == LQ_OK) rc = run_to_stop(lat, fp->max_steps, out);
     // the next call on this GPU may reuse the array: nothing may continue from it
     lat->bound = false;
@@ -1317,7 +1328,7 @@ int lq_batch_step(lq_batch* b, int64_t n_steps, lq_fire_report* reports) {
                 d.v[k] = bb.v[k];
                 d.F[k] = bb.F[k];
             }
-            d.partials = m->d_partials;
+            d.partials = step_partials(m);
             d.st = m->d_state;
             d.nblocks = (int)n_step_blocks(m->dev);
             tile_off[at++] = group[g].blocks;

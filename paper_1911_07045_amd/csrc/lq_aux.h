@@ -11,9 +11,6 @@ namespace lq {
 // Device address of the fixed workspace of lq_minimize_noalloc on `device`
 // (which must be current): looked up once per device, then cached.
 int noalloc_workspace(int device, void** out);
-// Its size: the limit that callers see, and room for the partial sums of
-// lattices in bricks (at most two slots per 256 sites, 32 bytes, twice).
-constexpr int64_t NOALLOC_ARRAY_BYTES = LQ_NOALLOC_WORKSPACE_BYTES + ((int64_t)256 << 10);
 
 // Streams of the copy-ceiling kernel (lq_stream_copy).
 constexpr int STREAMS_MAX = 16;

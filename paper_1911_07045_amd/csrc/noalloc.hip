@@ -12,7 +12,7 @@
 
 #include "lq_aux.h"
 
-static __device__ __align__(256) unsigned char scratch[lq::NOALLOC_ARRAY_BYTES];
+static __device__ __align__(256) unsigned char scratch[LQ_NOALLOC_WORKSPACE_BYTES];
 
 namespace lq {
 
