@@ -142,7 +142,10 @@ __device__ __forceinline__ void brick_block(const LatDev& L, const Bufs<T>& b, c
                     s[0] = wave_sum(s[0]); s[1] = wave_sum(s[1]); s[2] = wave_sum(s[2]); s[3] = wave_max(s[3]);
                 }
                 if (tid <= CTL_WORDS) ((uint32_t*)&ctl)[tid] = word;
+                // lane 63 reads what the lanes of its wave wrote: a compiler
+                // fence that no lane's path may be moved across, and a wait
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_wave_barrier();
                 if (tid == 63) control();
             }
         } else if (k >= 2 && tid < nblocks) {
