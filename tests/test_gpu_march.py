@@ -1,6 +1,14 @@
-"""The marching kernels: batches, minimizers, stops, resumes and divergence on
-lattices above the sizes that step in bricks.
+"""The marching kernels on lattices above the sizes that step in bricks, and
+bricks whose partial sums the whole block adds up: batches, the minimizers
+against the oracle, stops inside a call, resumes and divergence.
+
+Tolerances: along a few FP64 steps 1e-10 relative, as elsewhere.  A few
+FP32 steps from the same state round q by 2^-24 each, which a force of slope up
+to some 60 turns into 4e-6 a step, next to 1e-5 of one evaluation on forces of order
+ten to a hundred: 5e-5 relative to the largest force, momentum or tensor.
 """
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -64,7 +72,15 @@ BATCHES = [
 ]
 
 
-@pytest.mark.parametrize("prec,members", BATCHES, ids=["f64_l23", "f64_l23_large", "f64_one", "f32_l23", "f32_l23_large"])
+# all in bricks: up to 256 of them, more, and more than a block has threads
+BRICK_BATCHES = [
+    ("f64", [("l23", (44, 40, 40)), ("l23", (24, 20, 18)), ("chiral", (70, 66, 75))]),
+    ("f32", [("one", (64, 64, 48)), ("one", (75, 66, 61)), ("one", (24, 20, 18))]),
+]
+
+
+@pytest.mark.parametrize("prec,members", BATCHES + BRICK_BATCHES,
+                         ids=["f64_l23", "f64_l23_large", "f64_one", "f32_l23", "f32_l23_large", "f64_bricks", "f32_bricks"])
 def test_batch_equals_alone_bitwise(prec, members):
     """A member follows its solo trajectory bit for bit, sums and steering
     included, over calls of odd and even length.  (Sums taken in another order
@@ -138,3 +154,111 @@ def test_stop_inside_a_call(prec, elastic, shape, method):
         rep = out[0][0]
         assert (rep["status"] == lqfire.CONVERGED and 0 < rep["step"] <= 40) if tol else \
             (rep["status"] == lqfire.MAX_STEPS and rep["step"] == cap)
+
+
+# precision, elastic terms, shape, periodic: both tile widths; rows of whole half
+# lines and ragged ones; state held by the cache and beyond it; bricks above 256
+# and above one per thread of a block
+BOXES = [("f64", "one", (64, 84, 80), (True, True, False)), ("f64", "one", (61, 96, 90), (True, True, True)),
+         ("f64", "one", (101, 150, 90), (False, True, True)), ("f64", "one", (64, 140, 130), (True, True, True)),
+         ("f64", "l23", (64, 84, 90), (True, False, True)), ("f64", "l23", (61, 96, 90), (True, True, True)),
+         ("f64", "l23", (65, 150, 130), (True, True, True)),
+         ("f64", "chiral", (64, 80, 90), (True, True, False)), ("f64", "chiral", (60, 92, 84), (True, True, True)),
+         ("f32", "one", (128, 96, 90), (True, True, True)), ("f32", "one", (100, 142, 120), (True, False, True)),
+         ("f32", "one", (301, 90, 84), (True, True, True)), ("f32", "one", (128, 140, 130), (True, True, False)),
+         ("f32", "l23", (64, 80, 84), (True, True, True)), ("f32", "l23", (61, 80, 90), (False, True, True)),
+         ("f32", "l23", (65, 190, 190), (True, True, True)), ("f32", "chiral", (64, 76, 84), (True, True, True)),
+         ("f32", "chiral", (60, 84, 84), (True, True, False))]
+BRICKS = [("f64", "one", (64, 64, 48), (True, True, True)), ("f32", "one", (75, 66, 61), (True, False, True)),
+          ("f64", "one", (75, 66, 61), (False, True, False)), ("f64", "l23", (44, 40, 40), (True, True, True)),
+          ("f32", "l23", (70, 66, 75), (True, True, False)), ("f64", "chiral", (70, 66, 75), (True, True, True))]
+
+
+def _close(got, ref, tol, floor=0.0):
+    err = np.abs(got.cpu().numpy().astype(np.float64) - ref).max()
+    assert err <= tol * max(floor, np.abs(ref).max()), f"{err:.3e}"
+
+
+@pytest.mark.parametrize("prec,elastic,shape,periodic", BOXES + BRICKS)
+def test_trajectory_against_the_oracle(ora, prec, elastic, shape, periodic):
+    """q, v and F of the three minimizers after calls of one and two steps."""
+    objs = _objects(shape)
+    recs = [dict(site=shape[0] * shape[1] + 1, law="nd", W=0.4, n0=(1.0, 2.0, 2.0))]
+    p = ora.Problem(shape, periodic, L1=2.32, objects=objs, site_records=recs, **ELASTIC[elastic])
+    lat = lqfire.Lattice(shape, periodic, prec, L1=2.32, **ELASTIC[elastic])
+    lat.set_boundaries(objs, recs)
+    dtype, tol = (torch.float64, 1e-10) if prec == "f64" else (torch.float32, 5e-5)
+    start = _dev(p.uniaxial(synth.random_directors(9, p.N)), dtype)
+    q0 = start.double().cpu().numpy()
+    for method, mu in (("fire", None), ("gd", 0.0), ("nesterov", 0.8)):
+        print(f"[march] oracle {prec} {elastic} {shape} {periodic} {method}", flush=True)
+        q, v, F = start.clone(), lat.zeros(), lat.empty()
+        if method == "fire":
+            prm = ora.fire_params(force_tol=0.0, max_steps=10 ** 6)
+            st, qo, vo, Fo = p.fire_init(prm, q0)
+            lat.fire_init(lqfire.make_fire_params(force_tol=0.0, max_steps=10 ** 6), q, v, F)
+        else:
+            prm = ora.descent_params(method, 2e-3, mu, force_tol=0.0, max_steps=10 ** 6)
+            st, qo, vo, Fo = p.descent_init(prm, q0)
+            lat.descent_init(lqfire.make_descent_params(method, 2e-3, mu, force_tol=0.0, max_steps=10 ** 6), q, v, F)
+        for n in (1, 2):
+            (p.fire_steps if method == "fire" else p.descent_steps)(prm, st, qo, vo, Fo, n)
+            rep = lat.fire_step(n)
+            assert rep.step == st.step and rep.status == lqfire.RUNNING
+            _close(F, Fo, tol)
+            _close(q, qo, tol, 1.0)
+            if method != "gd":
+                _close(v, vo, tol)
+            assert abs(rep.normF - st.normF) <= tol * st.normF
+    lat.close()
+
+
+RESUMES = [("f64", "one", (101, 150, 90)), ("f64", "l23", (64, 132, 140)), ("f64", "chiral", (64, 132, 140)),
+           ("f32", "one", (128, 140, 130)), ("f32", "l23", (65, 190, 190)), ("f64", "one", (75, 66, 61))]
+
+
+@pytest.mark.parametrize("method", ["fire", "gd", "nesterov"])
+@pytest.mark.parametrize("prec,elastic,shape", RESUMES)
+def test_resume_at_an_odd_step(prec, elastic, shape, method):
+    """A run cut after an odd number of steps, in one binding or re-bound with
+    the saved report, equals the uncut run bit for bit."""
+    print(f"[march] resume {prec} {elastic} {shape} {method}", flush=True)
+    lat, *whole = _start(prec, elastic, shape, method)
+    rep = lat.fire_step(140).as_dict()
+    lat.close()
+    lat, *cut = _start(prec, elastic, shape, method)
+    saved = lat.fire_step(57)
+    # the last 83 steps on another handle, from copies
+    copy = [f.clone() for f in cut]
+    other = _lattice(shape, prec, elastic)
+    if method == "fire":
+        other.fire_init(lqfire.make_fire_params(force_tol=0.0, max_steps=10 ** 6), *copy, resume=saved)
+    else:
+        mu = 0.8 if method == "nesterov" else 0.0
+        other.descent_init(lqfire.make_descent_params(method, 2e-3, mu, force_tol=0.0, max_steps=10 ** 6), *copy, resume=saved)
+    assert torch.equal(copy[2], cut[2])
+    again = other.fire_step(83).as_dict()
+    for n in (1, 3, 79):
+        rest = lat.fire_step(n).as_dict()
+    for state, r in ((cut, rest), (copy, again)):
+        assert r == rep
+        assert all(torch.equal(a, b) for a, b in zip(state, whole))
+    lat.close()
+    other.close()
+
+
+@pytest.mark.parametrize("method", ["gd", "nesterov"])
+@pytest.mark.parametrize("prec,elastic,shape", [("f64", "l23", (64, 84, 90)), ("f32", "one", (128, 96, 90)), ("f64", "one", (75, 66, 61))])
+def test_divergence_is_reported(prec, elastic, shape, method):
+    """A step above the stability limit blows up: the call ends with LQ_ENONFINITE
+    where the sums are no longer finite, and later calls stay there."""
+    print(f"[march] divergence {prec} {elastic} {shape} {method}", flush=True)
+    lat = _lattice(shape, prec, elastic)
+    q, v, F = _random_start(lat), lat.zeros(), lat.empty()
+    lat.descent_init(lqfire.make_descent_params(method, 0.2, 0.8, force_tol=0.0, max_steps=10 ** 6), q, v, F)
+    L, r = lqfire.lib(), lqfire.FireReport()
+    assert L.lq_fire_step(lat.h, 600, C.byref(r)) == lqfire.LQ_ENONFINITE
+    assert r.status == lqfire.NONFINITE and 0 < r.step < 600
+    step = r.step
+    assert L.lq_fire_step(lat.h, 5, C.byref(r)) == lqfire.LQ_ENONFINITE and r.step == step
+    lat.close()

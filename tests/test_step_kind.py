@@ -45,6 +45,13 @@ def test_boxes_of_the_gpu_tests():
         assert got >= {(e, k) for e in terms for k in ("narrow", "wide")} and "bricks" in {k for _, k in got}
     got = {(prec, kind(shape, prec, elastic)) for prec, elastic, shape in test_gpu_march.STOPS}
     assert got == {(p, k) for p in ("f32", "f64") for k in ("narrow", "wide", "bricks")}
+    got = {(prec, elastic, kind(shape, prec, elastic, periodic)) for prec, elastic, shape, periodic in test_gpu_march.BOXES}
+    assert got == {(p, e, k) for p in ("f32", "f64") for e in ELASTIC for k in ("narrow", "wide")}
+    bricks = [(prec, elastic, shape) for prec, elastic, shape, _ in test_gpu_march.BRICKS]
+    bricks += [(prec, elastic, shape) for prec, members in test_gpu_march.BRICK_BATCHES for elastic, shape in members]
+    assert {kind(shape, prec, elastic) for prec, elastic, shape in bricks} == {"bricks"}
+    got = [kind(shape, prec, elastic) for prec, elastic, shape in test_gpu_march.RESUMES]
+    assert got == ["wide"] * 5 + ["bricks"]
 
 
 def test_bad_arguments():
