@@ -509,7 +509,10 @@ static int step_kind_for(const lq_params& p, bool l23) {
 // planes z - 1 .. z + 1 are all full bulk sites.  FP32: when the marching plan
 // gives them the bulk form (its tiles are wider, so fewer planes do).  The two
 // forms round differently and FP32 rounding grows along a relaxation; this way
-// an FP32 trajectory does not depend on the family of kernels that steps it.
+// each site's force in FP32 is the same in both families of kernels.  (Their sums
+// are taken over other parts in another order and agree to FP64 rounding, which
+// can turn the last bit of a steering coefficient; FP32 trajectories measured
+// equal bit for bit over 1200 steps of 15 boxes.)
 static std::vector<uint8_t> plan_bricks(const lq_params& p, bool l23, const std::vector<uint8_t>& mask, int device) {
     int64_t S[3], nb[3];
     brick_size(l23, S);

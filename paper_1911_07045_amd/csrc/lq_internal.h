@@ -48,10 +48,11 @@ int rasterize(const lq_params& p, double S0, const lq_object* objs, int32_t n_ob
 // 1024 threads for the one-constant FP32 kernel (at most 128 VGPRs, four
 // waves per SIMD), 512 for FP32 with L2/L3/L4 and for one-constant FP64,
 // 256 (64 x 4) for FP64 with L2/L3/L4.  Lattices narrower than a wide tile
-// (the small boxes of a serving batch) use a narrow tile instead: 64 x 8 in
-// FP32 (on a stream of 16-64-site boxes it gave half the median latency of
-// 32 x 8), 32 x 8 in FP64.  WAVES is the number of waves per SIMD a kernel
-// is held to (1: no constraint).
+// use a narrow tile instead: 64 x 8 in FP32, 32 x 8 in FP64.  (The sizes date
+// from when small boxes marched: on a stream of 16-64-site FP32 boxes 64 x 8
+// gave half the median latency of 32 x 8.  Small boxes step in bricks now; the
+// tall and thin ones that march on these tiles were not tried on others.)
+// WAVES is the number of waves per SIMD a kernel is held to (1: no constraint).
 #ifndef LQ_TILE_X_F32
 #define LQ_TILE_X_F32 128
 #endif

@@ -59,6 +59,7 @@ __device__ __forceinline__ void bst_p(__amdgpu_buffer_rsrc_t r, uint32_t voff, u
 // run-time one put a branch in the march loop that cost 1.5%.
 template <typename T, bool L23, bool ROWS>
 constexpr int store_policy() { return (L23 && sizeof(T) == 4) || !ROWS ? 0 : 2; }
+// (15 values a site and buffer, also for gradient descent, whose steps use ten of them.)
 template <typename T>
 __host__ __device__ inline bool state_fits_cache(int64_t N) { return 2 * 15 * N * (int64_t)sizeof(T) <= (int64_t)256 << 20; }
 template <typename T>
@@ -328,9 +329,9 @@ __device__ __forceinline__ void anch_load(const LatDev& L, int arow1, AnchRow<T>
 // -dE/dq at the stencil centre (a simulated site with mask m0).  Where m0
 // carries the anchoring bit, the site's anchoring form is AR (wide tiles,
 // loaded ahead by the caller) or row arow1 - 1 of the FP64 forms, read here
-// (narrow tiles: on the serving stream of small boxes this measured a lower
-// tail latency than the early loads; FP64 L2/L3: the 40 registers of an early
-// row are what keeps that kernel from two waves per SIMD).
+// (bricks, and narrow tiles, where early loads measure within 2% either way; FP64
+// L2/L3: the 40 registers of an early row are what keeps that kernel from two
+// waves per SIMD).
 template <typename T, bool L23, bool L4, bool BULK, int W, class ST>
 __device__ __forceinline__ void site_force(const ST& P, uint32_t m0,
                                            const LatDev& L, const AnchRow<T>& AR, int arow1, T F[5]) {
@@ -517,7 +518,7 @@ __device__ __forceinline__ void site_force(const ST& P, uint32_t m0,
         for (int c = 0; c < 5; ++c) g[c] += Kq[c];
     }
     if (!BULK && (W == 0 || (L23 && sizeof(T) == 8)) && (m0 & M_ANCH)) {
-        // narrow tiles: the row of the FP64 form, read here
+        // the row of the FP64 form, read here
         const int at = arow1 - 1;
         if (at >= 0) {
             const double* d = L.anch_data + ANCH_STRIDE * (int64_t)at;

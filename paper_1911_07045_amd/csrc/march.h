@@ -297,9 +297,9 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
         // anchoring forms of plane j - 1, whose force this iteration
         // evaluates.  Wide tiles issue them first, so that they arrive while
         // plane j is drifted and the block meets at the barrier.  Narrow tiles
-        // (the small boxes of a batch) read the FP64 rows inside the force
-        // instead: on a stream of small boxes the early loads raised the tail
-        // latency.  So do the FP64 L2/L3 kernels (registers; see site_force).
+        // read the FP64 rows inside the force instead (us per FIRE step with
+        // and without: FP32 60x300x300 169.0 and 169.4, L4 262 and 268; FP64 390.6
+        // and 389.2).  So do the FP64 L2/L3 kernels (registers; see site_force).
         AnchRow<T> A;
         if (!BULK && W == 1 && !(L23 && sizeof(T) == 8)) {
             const int f = j - 1;
@@ -339,8 +339,11 @@ __device__ __forceinline__ void march(const LatDev& L, const T* __restrict__ q_i
             T F[5];
             // a plane whose 3 x 3 x 3 neighbourhoods are all full bulk sites
             // takes the bulk evaluation also inside a boundary tile (wide
-            // tiles only: the narrow ones serve small boxes, where few planes
-            // qualify and the extra code costs registers).  The first two
+            // tiles only.  That was settled when small boxes marched on narrow
+            // tiles, few of whose planes qualify.  Boxes that march on them
+            // now would gain with L2/L3: with a sphere and two walls 60x300x300
+            // takes 241 us a step in FP32 and 866 in FP64, 174 and 420 with the
+            // bulk evaluation; one-constant 169 and 389, 174 and 391).  The first two
             // iterations have no plane of the chunk to evaluate (their stores
             // are dropped): the L2/L3 kernels compute no force there (in the
             // one-constant kernels the branch split the loop body and measured

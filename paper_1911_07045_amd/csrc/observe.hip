@@ -13,20 +13,21 @@ namespace lq {
 // Energy, in FP64: per-term block partials, summed in block order by a second
 // kernel of one block.  (With the sum in the last block to take a ticket, the
 // blocks' atomics and fences on one address took 25 ns each, 100 of the 110 us
-// of a 128^3 energy.)  Bound by FP64 arithmetic and FP32-to-FP64 conversions
-// (256^3 FP32 one-constant 440 -> 146 us per call, where its 336 MB take 68;
-// L2/L3 578 -> 221; 128^3 110 -> 41, of which 20 are two launches and a wait);
-// loading the neighbours one plane ahead measured equal to 15% slower, 2048 or
-// 8192 blocks instead of 4096 equal or slower.  A thread owns one column (x, y)
-// and walks zc planes of it upwards with the own and the next plane's q in
-// registers.  A block takes 256 columns of one run of planes, or (PACKED) the
-// columns' runs follow each other over the threads: boxes of few columns would
-// leave most of such blocks idle (3x3x100000 FP32 207 us, packed 32; L2/L3 280
-// and 40; 4x4x30000 77 and 26), while in full blocks z is uniform (256^3 FP32
-// 145.9, packed 147.0).  Bonds are taken
-// once, from their lower end, with the weights of both ends (1/n_k each, 1/2
-// in the bulk); the cross-axis and chiral terms need the mean differences of
-// the site and so both neighbours of every axis.
+// of a 128^3 energy.)  Bound by the L1 data path, 82% busy with 18 loads a site,
+// beside a vector ALU that is 61% busy, two fifths of it FP64 arithmetic (256^3
+// FP32 one-constant 440 -> 146 us per call, 130 of them this kernel, where its
+// 336 MB take 68; L2/L3 578 -> 221; 128^3 110 -> 41, of which 20 are two launches
+// and a wait); loading the neighbours one plane ahead measured equal to 15%
+// slower, 2048 or 8192 blocks instead of 4096 equal or slower.  A thread owns one
+// column (x, y) and walks zc planes of it upwards with the own and the next
+// plane's q in registers.  A block takes 256 columns of one run of planes, or
+// (PACKED) the columns' runs follow each other over the threads: boxes of few
+// columns would leave most of such blocks idle (3x3x100000 FP32 207 us, packed 32;
+// L2/L3 280 and 40; 4x4x30000 77 and 26), while in full blocks z is uniform (256^3
+// FP32 145.9, packed 147.0).  Bonds are taken once, from their lower end, with the
+// weights of both ends (1/n_k each, 1/2 in the bulk); the cross-axis and chiral
+// terms need the mean differences of the site and so both neighbours of every
+// axis.
 template <typename T, bool L23, bool PACKED>
 __global__ __launch_bounds__(256) void k_energy(LatDev L, const T* __restrict__ q, int zc, double* partials) {
     __shared__ double scratch[4][4];
@@ -226,11 +227,13 @@ __global__ __launch_bounds__(SUM_THREADS) void k_energy_sum(const double* partia
 // The cosine: c = cos(acos(r)/3) is the largest root of 4 c^3 - 3 c = r, taken
 // by Newton's iteration in FP64 from a start good to 3e-5 (acos from Abramowitz
 // and Stegun 4.4.45, cos from its series).  The derivative 12 c^2 - 3 enters in
-// FP32: with its 1e-7 the errors fall as 3e-5, 1e-8, 1e-15, below 1e-20 for
-// r >= -0.98.  With acos and cos for every site the kernel was bound by its
-// arithmetic (192^3 FP32 121 -> 99 us per call, 128^3 79 -> 52, 20 of them
-// launches and the wait).  (Below that the root is nearly double and takes the rounding of
-// r to its square root: the caller goes by sqrt, acos and cos.)
+// FP32: with its 1e-7 the truncation errors fall as 3e-5, 1e-8, 1e-15, below 1e-20
+// for r >= -0.98, and the rounding of the last FP64 correction (about one spacing
+// of the result) is what remains.  (Below that the root is nearly double and takes
+// the rounding of r to its square root: the caller goes by sqrt, acos and cos.)
+// With acos and cos for every site the kernel was bound by its arithmetic (192^3
+// FP32 121 -> 103 us per call, 128^3 79 -> 52, 20 of them launches and the wait);
+// now the vector ALU is 58% busy and the memory gives 3.3 of 4.9 TB/s.
 __device__ __forceinline__ double cos_third(double r) {
     const float x = fabsf((float)r);
     float t = __builtin_amdgcn_sqrtf(fmaxf(1.0f - x, 0.0f)) *
