@@ -96,8 +96,12 @@ struct Stencil {
 // with the non-temporal one.  Upwards always march the FP64 L4 kernels
 // (201x163x95 with a colloid 358, in turn 363) and the L2/L3 kernels of narrow
 // tiles (FP64 24x400x400 508, in turn 517, gradient descent 481 and 495; FP32
-// 3x64x4000 297 and 316, 60x300x300 211 and 216) and of state that stays in the
-// cache either way (FP32 L4 150x100x100 75.8 and 78.7, 130x140x70 72.4 and 74.8).
+// 3x64x4000 297 and 316, 60x300x300 211 and 216; the choice itself costs there what
+// it gives, and only between one and two cache sizes would marching in turn be
+// 2-4% faster: FP64 60x170x170 124 and 119).  State that fits the cache marches
+// in turn as well: near its size that is where the gain is largest (FP32 L2/L3
+// 128^3 slab 63 us a step, 78 upwards), far below it nothing is lost but 3% with
+// L4 (FP32 150x100x100 78.7, 75.8 upwards).
 template <typename T, bool L23, int W>
 __device__ __forceinline__ void ring_pos(int r, int& px, int& py) {
     constexpr int PX = Tile<T, L23, W>::PX, PY = Tile<T, L23, W>::PY;
@@ -477,8 +481,7 @@ __device__ __forceinline__ void step_block(const LatDev& L, const Bufs<T>& b, co
     if (STEP) {
         if (dc_begin(st, partials, nblocks, k, bid, scratch, ctl_d, ctl_i)) return;
         const int cur = ctl_i[0] & 1;
-        const bool upwards = (L23 && (W == 0 || state_fits_cache<T>(L.N))) ||
-                             (L4 && sizeof(T) == 8 && (!BATCH || L.L4 != 0.0));
+        const bool upwards = (L23 && W == 0) || (L4 && sizeof(T) == 8 && (!BATCH || L.L4 != 0.0));
         down = !upwards && (ctl_i[0] & 2) != 0;
         const double dtd = ctl_d[0], c_v = ctl_d[1], c_F = ctl_d[2], mu = ctl_d[3];
         // selects rather than indexing by cur, which would put b in scratch

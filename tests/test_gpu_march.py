@@ -62,7 +62,7 @@ def _fire(shape, prec, elastic, seed=5):
 
 # precision, members (elastic terms, shape): narrow and wide marching tiles and
 # a box that steps in bricks; L2/L3 and chiral members share a batch; the second
-# and the last batch hold boxes beyond the cache, whose steps march both ways
+# and the last batch hold boxes beyond the cache
 BATCHES = [
     ("f64", [("l23", (64, 84, 90)), ("chiral", (64, 80, 90)), ("l23", (61, 96, 90)), ("chiral", (60, 92, 84)), ("l23", (24, 20, 18))]),
     ("f64", [("l23", (64, 132, 140)), ("chiral", (64, 132, 140)), ("l23", (61, 140, 150)), ("chiral", (61, 96, 100)), ("l23", (24, 20, 18))]),
