@@ -61,7 +61,7 @@ template <typename T, bool L23, bool ROWS>
 constexpr int store_policy() { return (L23 && sizeof(T) == 4) || !ROWS ? 0 : 2; }
 // (15 values a site and buffer, also for gradient descent, whose steps use ten of them.)
 template <typename T>
-inline bool state_fits_cache(int64_t N) { return 2 * 15 * N * (int64_t)sizeof(T) <= (int64_t)256 << 20; }
+__host__ __device__ inline bool state_fits_cache(int64_t N) { return 2 * 15 * N * (int64_t)sizeof(T) <= (int64_t)256 << 20; }
 template <typename T>
 inline bool whole_rows(int nx) { return ((size_t)nx * sizeof(T)) % 64 == 0; }
 

@@ -94,14 +94,12 @@ struct Stencil {
 // per step, FP32 L2/L3 201x163x95 slab 145.7 -> 134.3, 256^3 437 -> 426;
 // one-constant 230x187x141 FP32 198 -> 181, FP64 371 -> 361) and is neutral
 // with the non-temporal one.  Upwards always march the FP64 L4 kernels
-// (201x163x95 with a colloid 358, in turn 363) and the L2/L3 kernels of narrow
-// tiles (FP64 24x400x400 508, in turn 517, gradient descent 481 and 495; FP32
-// 3x64x4000 297 and 316, 60x300x300 211 and 216; the choice itself costs there what
-// it gives, and only between one and two cache sizes would marching in turn be
-// 2-4% faster: FP64 60x170x170 124 and 119).  State that fits the cache marches
-// in turn as well: near its size that is where the gain is largest (FP32 L2/L3
-// 128^3 slab 63 us a step, 78 upwards), far below it nothing is lost but 3% with
-// L4 (FP32 150x100x100 78.7, 75.8 upwards).
+// (201x163x95 with a colloid 358, in turn 363) and, where the cache holds the
+// state, the L2/L3 kernels of narrow tiles, which lose to the choice itself (TURN:
+// a kernel has it; FP32 3x64x4000 297, in turn 316, 5x400x200 130 and 139; FP64
+// 60x132x132 with a sphere 148 and 151).  Beyond the cache those march in turn too
+// (FP64 50x250x250 211, upwards 221; FP32 34x300x300 139 and 147), as do wide tiles
+// on either side of its size (FP32 L2/L3 128^3 slab 63 us a step, 78 upwards).
 template <typename T, bool L23, int W>
 __device__ __forceinline__ void ring_pos(int r, int& px, int& py) {
     constexpr int PX = Tile<T, L23, W>::PX, PY = Tile<T, L23, W>::PY;
@@ -457,10 +455,11 @@ __device__ bool dc_begin(FireDev* st, const double* partials, int nblocks, int k
 // is the lattice's own tile count; partials are indexed by tile, so the
 // reduction order does not depend on how blocks are dispatched.  The
 // controller of step k - 1 runs at the start (dc_begin); the partials of
-// step k go to slot k & 1.  BATCH: L4 says only that members may be chiral;
-// one that is not marches in the direction that its kernel alone takes, since
-// the order of a block's sums follows the march.
-template <typename T, bool L23, bool L4, int MODE, int W, bool ROWS, bool BATCH = false>
+// step k go to slot k & 1.  TURN: steps march up and down in turn.  BATCH: the
+// kernel serves members of any size, and L4 says only that they may be chiral;
+// each marches in the direction that its kernel alone takes, since the order of
+// a block's sums follows the march.
+template <typename T, bool L23, bool L4, int MODE, int W, bool ROWS, bool TURN, bool BATCH = false>
 __device__ __forceinline__ void step_block(const LatDev& L, const Bufs<T>& b, const T* __restrict__ qin,
                                            T* __restrict__ Fout, double* partials, FireDev* st,
                                            int nblocks, int bid, int k) {
@@ -481,7 +480,8 @@ __device__ __forceinline__ void step_block(const LatDev& L, const Bufs<T>& b, co
     if (STEP) {
         if (dc_begin(st, partials, nblocks, k, bid, scratch, ctl_d, ctl_i)) return;
         const int cur = ctl_i[0] & 1;
-        const bool upwards = (L23 && W == 0) || (L4 && sizeof(T) == 8 && (!BATCH || L.L4 != 0.0));
+        const bool upwards = !TURN || (L4 && sizeof(T) == 8 && (!BATCH || L.L4 != 0.0)) ||
+                             (BATCH && L23 && W == 0 && state_fits_cache<T>(L.N));
         down = !upwards && (ctl_i[0] & 2) != 0;
         const double dtd = ctl_d[0], c_v = ctl_d[1], c_F = ctl_d[2], mu = ctl_d[3];
         // selects rather than indexing by cur, which would put b in scratch
@@ -528,13 +528,13 @@ __device__ __forceinline__ void step_block(const LatDev& L, const Bufs<T>& b, co
 // common L2/L3 kernels do not carry its registers).  TWO: held to two waves
 // per SIMD (the FP64 L2/L3 kernel for lattices whose one-wave chunks would be
 // short; LatDev::two_waves).
-template <typename T, bool L23, bool L4, int MODE, int W, bool TWO = false, bool ROWS = true>
+template <typename T, bool L23, bool L4, int MODE, int W, bool TWO = false, bool ROWS = true, bool TURN = true>
 __global__ __launch_bounds__((Tile<T, L23, W>::N)) __attribute__((amdgpu_waves_per_eu(L4 ? 1 : (TWO ? 2 : Tile<T, L23, W>::WAVES)))) void k_march(LatDev L, Bufs<T> b, const T* __restrict__ qin,
                                                     T* __restrict__ Fout, double* partials,
                                                     FireDev* st, int k) {
     const int nblocks = (int)gridDim.x;
     const int bid = xcd_block((int)blockIdx.x, nblocks);
-    step_block<T, L23, L4, MODE, W, ROWS>(L, b, qin, Fout, partials, st, nblocks, bid, k);
+    step_block<T, L23, L4, MODE, W, ROWS, TURN>(L, b, qin, Fout, partials, st, nblocks, bid, k);
 }
 
 // ---------------------------------------------------------------------------
@@ -553,7 +553,7 @@ __global__ __launch_bounds__((Tile<T, L23, W>::N)) __attribute__((amdgpu_waves_p
         b.q[i] = (T*)M.q[i]; b.v[i] = (T*)M.v[i]; b.F[i] = (T*)M.F[i];
     }
     const LatDev& L = M.L;
-    step_block<T, L23, L23, MODE_FIRE, W, true, true>(L, b, nullptr, nullptr, M.partials, M.st, M.nblocks,
+    step_block<T, L23, L23, MODE_FIRE, W, true, true, true>(L, b, nullptr, nullptr, M.partials, M.st, M.nblocks,
                                           (int)blockIdx.x - off[m], k);
 }
 
@@ -577,8 +577,17 @@ static int blocks_per_cu_t(bool l23, bool l4, int wide) {
 template <typename T, bool L23, bool L4, int MODE, int W, bool TWO, bool ROWS>
 static void launch_one(const LatDev& L, const Bufs<T>& b, const void* q, void* F, double* partials, FireDev* st, int k,
                        hipStream_t s) {
-    k_march<T, L23, L4, MODE, W, TWO, ROWS><<<dim3((unsigned)n_step_blocks(L)), Tile<T, L23, W>::N, 0, s>>>(
-        L, b, (const T*)q, (T*)F, partials, st, k);
+    constexpr bool F64 = sizeof(T) == 8;
+    const dim3 g((unsigned)n_step_blocks(L));
+    // narrow L2/L3 steps within the cache (its FP64 kernels store with ROWS false there)
+    if constexpr (L23 && W == 0 && MODE != MODE_FORCE && !(F64 && (L4 || ROWS))) {
+        if (state_fits_cache<T>(L.N)) {
+            k_march<T, L23, L4, MODE, W, TWO, ROWS, false><<<g, Tile<T, L23, W>::N, 0, s>>>(L, b, (const T*)q, (T*)F,
+                                                                                          partials, st, k);
+            return;
+        }
+    }
+    k_march<T, L23, L4, MODE, W, TWO, ROWS><<<g, Tile<T, L23, W>::N, 0, s>>>(L, b, (const T*)q, (T*)F, partials, st, k);
 }
 
 template <typename T, int MODE, int W>

@@ -68,7 +68,7 @@ BATCHES = [
     ("f64", [("l23", (64, 132, 140)), ("chiral", (64, 132, 140)), ("l23", (61, 140, 150)), ("chiral", (61, 96, 100)), ("l23", (24, 20, 18))]),
     ("f64", [("one", (64, 84, 80)), ("one", (61, 96, 90)), ("one", (24, 20, 18))]),
     ("f32", [("l23", (64, 80, 84)), ("chiral", (64, 76, 84)), ("l23", (61, 80, 90)), ("chiral", (60, 84, 84)), ("l23", (24, 20, 18))]),
-    ("f32", [("l23", (64, 192, 190)), ("chiral", (64, 192, 190)), ("l23", (61, 80, 90)), ("chiral", (60, 84, 84)), ("l23", (24, 20, 18))]),
+    ("f32", [("l23", (64, 192, 190)), ("chiral", (64, 192, 190)), ("l23", (61, 200, 190)), ("chiral", (60, 202, 190)), ("l23", (24, 20, 18))]),
 ]
 
 
